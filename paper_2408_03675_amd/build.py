@@ -26,6 +26,11 @@ SOURCES = ["score.hip", "select.hip", "compact.hip", "attention.hip", "api.cpp",
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wall", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include")]
+# Per-source options.  attention.hip: MFMA results in vector registers unless
+# the source asks for accumulation registers (its logits feed vector
+# instructions at once; copies out of accumulation registers would cost as
+# much as the exponentials' FMAs).
+SOURCE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _hipcc():
@@ -38,7 +43,7 @@ def _hipcc():
 def _compile(src):
     obj = os.path.join(BUILD, src + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else []
-    cmd = [_hipcc()] + HIP_FLAGS + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [_hipcc()] + HIP_FLAGS + SOURCE_FLAGS.get(src, []) + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(x for x in r.stderr.splitlines() if noise not in x)

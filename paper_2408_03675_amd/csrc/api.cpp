@@ -579,7 +579,6 @@ int nacl_attention(const nacl_problem* p, const void* q, const void* k, const vo
   a.H = p->H;
   a.G = g;
   a.L = p->L;
-  a.n_tiles = (p->L + 127) / 128;
   a.c2 = p->sm_scale * 1.4426950408889634f;
   for (int i = 0; i < 3; ++i) {
     a.qs[i] = p->q_stride[i];
@@ -591,7 +590,7 @@ int nacl_attention(const nacl_problem* p, const void* q, const void* k, const vo
   a.v = static_cast<const __bf16*>(v);
   a.out = static_cast<__bf16*>(out);
   a.lse = lse;
-  if ((int64_t)a.B * Hq * a.n_tiles >= ((int64_t)1 << 31))
+  if ((int64_t)a.B * Hq * ((p->L + 127) / 128) >= ((int64_t)1 << 31))
     return fail(NACL_ERR_UNSUPPORTED, "too many query tiles");
   hipError_t e = nacl::launch_attention(a, p->D, p->proxy_pos_dev, p->P, lse_proxy, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "attention kernel");

@@ -192,7 +192,9 @@ hipError_t launch_append(const AppendLaunch& L, hipStream_t stream);
 // Causal attention of the prefill with each row's log-sum-exp (attention.hip).
 struct AttnLaunch {
   int B, H, G, L;      // batch, K/V heads, query heads per K/V head, rows
-  int n_tiles;         // 128-row query tiles per head
+  // Set by the launcher: query tiles per head, whole heads per XCD, and how
+  // many of those run together.
+  int n_tiles, heads_x, group;
   float c2;            // logit scale times log2(e)
   int64_t qs[3], ks[3], vs[3];  // element strides (q: per query head)
   const __bf16* q;

@@ -168,3 +168,52 @@ def test_attention_rejects_unsupported():
     prob = nacl.Problem.from_tensors(qb, qb, qb, [3])
     with pytest.raises(nacl.NaclError):
         nacl.attention(prob, qb, qb, qb, lse_proxy=True)  # no proxy_pos_dev
+
+
+# Edges of the work-group forms: 128 or 256 rows per work-group (the second
+# from 64 work-groups of 256 rows on), waves of 64 rows, tiles of 64 keys,
+# heads that 8 XCDs do not divide, and groups of heads sharing K and V.
+TILE_CASES = [
+    # B, H, q_group, L, D
+    (1, 1, 1, 63, 128), (1, 1, 1, 65, 64), (1, 3, 1, 127, 128), (2, 5, 1, 193, 64),   # 128-row work-groups
+    (1, 9, 1, 320, 128), (1, 4, 2, 255, 64),
+    (1, 67, 1, 65, 128), (2, 9, 4, 192, 64), (1, 64, 1, 256, 128), (4, 17, 1, 129, 64),  # 256-row work-groups
+    (1, 33, 1, 321, 128), (1, 9, 8, 257, 64), (1, 16, 1, 1025, 128),
+]
+
+
+@pytest.mark.parametrize("B,H,g,L,D", TILE_CASES)
+def test_attention_tile_edges(B, H, g, L, D):
+    print("attention tiles", B, H, g, L, D, file=sys.stderr, flush=True)
+    w = custom("edges", B, H, L, D, 1, dtype="bf16", data_seed=B + 3 * H + L)
+    q, k, v = make_grouped_layer(w, g, device="cuda")
+    prob = nacl.Problem.from_tensors(q, k, v, w.proxy_pos)
+    out, lse, _ = nacl.attention(prob, q, k, v)
+    torch.cuda.synchronize()
+    _check(out, lse, q, k, v, prob.c.sm_scale, g, f"{B}x{H}x{g} L{L} D{D}")
+
+
+@pytest.mark.parametrize("D", (64, 128))
+@pytest.mark.parametrize("H", (2, 64))
+def test_attention_rising_logits(D, H):
+    """Keys whose logits pass every earlier one by far (the reference of the
+    exponentials has to move, tile after tile and by more than one step), and
+    rows whose first tile holds the largest by far.  Logits reach a few
+    hundred, so the log-sum-exp is held to 1e-4 plus 2^-22 of its size (two
+    roundings of a product and a sum in fp32)."""
+    L = 700
+    w = custom("rise", 1, H, L, D, 1, dtype="bf16", data_seed=D + H)
+    q, k, v = make_grouped_layer(w, 1, device="cuda")
+    q = q.abs()
+    up = torch.ones(L, device="cuda")
+    for j, x in ((70, 3.0), (200, 9.0), (201, 10.0), (400, 30.0), (640, 60.0)):
+        up[j] = x
+    k = (k.abs() * up[None, None, :, None]).to(torch.bfloat16)
+    k[:, 1::2] = k[:, 1::2].flip(2)
+    prob = nacl.Problem.from_tensors(q, k, v, w.proxy_pos)
+    out, lse, _ = nacl.attention(prob, q, k, v)
+    torch.cuda.synchronize()
+    Or, lr = causal_attention(_f64(q), _f64(k), _f64(v), prob.c.sm_scale)
+    assert np.isfinite(_f64(out)).all()
+    assert np.abs(_f64(out) - Or).max() <= O_TOL * np.abs(_f64(v)).max()
+    assert (np.abs(_f64(lse) - lr) <= LSE_ATOL + 2.0 ** -22 * np.abs(lr)).all()
