@@ -26,11 +26,11 @@ SOURCES = ["score.hip", "select.hip", "compact.hip", "attention.hip", "api.cpp",
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wall", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include")]
-# Per-source options.  attention.hip: MFMA results in vector registers unless
-# the source asks for accumulation registers (its logits feed vector
-# instructions at once; copies out of accumulation registers would cost as
-# much as the exponentials' FMAs).
-SOURCE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+# Per-source options.  MFMA results in vector registers unless the source asks
+# for accumulation registers: the logits feed vector instructions at once, and
+# copies out of accumulation registers would cost as much as the exponentials'
+# FMAs.
+SOURCE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for src in ("attention.hip", "score.hip")}
 
 
 def _hipcc():

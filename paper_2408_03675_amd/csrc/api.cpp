@@ -267,23 +267,60 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
     if (items >= 4 * 2 * (int64_t)cus) sc.tpw = t;
   }
   sc.chunk_keys = sc.tpw * nacl::kScoreWaves * 16;
-  // The proxy-split kernel takes fixed items of kSplitChunkKeys keys.
-  if (nacl::score_uses_split(p->dtype, p->D, rows_of(p))) sc.chunk_keys = nacl::kSplitChunkKeys;
+  const int rows = rows_of(p);
+  sc.n_psplit = nacl::score_psplit(p->dtype, p->D, rows);
+  auto items_of = [&](int keys) { return (int64_t)BH * ((p->L + keys - 1) / keys); };
+  if (p->dtype == NACL_BF16) {
+    // Small launches: both passes with the keys held, up to one chunk of 512
+    // keys per CU.  32 heads of 4096 keys, 64 rows: 29.8 us, by tiles 39.0; 6
+    // heads of 32k keys, 400 rows: 85, in groups 258.  Two chunks per CU read
+    // one of them twice, which 65 to 128 rows still repay (96 rows, 512 chunks:
+    // 55 against 66), fewer rows do not (64 rows: 50 against 44; the tile
+    // kernel holds up to 64 with twice the work-groups) nor do more (200 rows,
+    // 400 chunks: 66.6, in the block kernel 62.4).
+    const bool two = rows > nacl::kKeysTwoMin && rows <= nacl::kKeysTwoMax;
+    const int64_t fuse_max = std::min<int64_t>((two ? 2 : 1) * (int64_t)cus, nacl::kKeysFuseMax);
+    if (!sc.lse_given && rows <= nacl::kSplitWideRows && items_of(nacl::kKeysThreads) <= fuse_max) {
+      sc.path = nacl::kScoreKeys;
+      sc.fused = 1;
+      sc.chunk_keys = nacl::kKeysThreads;
+    } else if (p->D == 128 && rows >= nacl::kSplitRows && (rows <= nacl::kBlockRows || rows >= nacl::kSplitWideRows)) {
+      // Rows that fit one work-group's registers (128, 129 to 256) or wide
+      // lists (512 and more: the matrix cores bound it, see score.hip).
+      sc.path = nacl::kScoreSplit;
+    } else if (rows > nacl::kSplitRows && rows <= nacl::kSplitWideRows) {
+      // D = 64, or 257 to 511 rows of D = 128.  32 heads of 32k keys, D = 64,
+      // 200 rows 130 us, by tiles 267; 8 heads of 128k keys, D = 128, 400
+      // rows and the caller's log-sum-exp 534, in two groups 722.
+      sc.path = nacl::kScoreKeys;
+    }
+    if (sc.path != nacl::kScoreTiles && !sc.fused) {
+      // Long items amortise their start; shorter ones where those of a pass
+      // number fewer than one per CU (of the block and wide kernels, two of
+      // which share a CU: two).  128 rows, 80 heads of 4096 keys: 160 items
+      // 83 us, 320 66; 16 heads of 32k keys: 256 items 95, 512 106.  256
+      // rows, 16 heads of 32k keys: 256 items 123, 512 103; 24 heads: 384
+      // items 141.5, 768 143.8.  400 rows, 12 heads of 32k keys: 384 items
+      // 127, 768 151.
+      const int per_cu = sc.path == nacl::kScoreSplit && rows != nacl::kSplitRows ? 2 : 1;
+      sc.chunk_keys = nacl::kSplitChunkKeys;
+      while (sc.n_psplit == 1 && sc.chunk_keys > nacl::kSplitChunkMin && items_of(sc.chunk_keys) < (int64_t)per_cu * cus)
+        sc.chunk_keys /= 2;
+    }
+  }
   sc.n_chunks = (p->L + sc.chunk_keys - 1) / sc.chunk_keys;  // <= l.n_chunks
-  sc.n_psplit = nacl::score_psplit(p->dtype, p->D, rows_of(p));
   sc.chunk_cnt = words + l.chunk_cnt_word;
   sc.colpart = reinterpret_cast<float*>(ws + l.colpart);
-  const int group_items = nacl::score_uses_split(p->dtype, p->D, rows_of(p)) ? NACL_SCORE_SPLIT_GROUP_ITEMS_PER_CU
-                                                                       : NACL_SCORE_GROUP_ITEMS_PER_CU;
+  const int group_items = sc.path == nacl::kScoreTiles ? NACL_SCORE_GROUP_ITEMS_PER_CU : NACL_SCORE_SPLIT_GROUP_ITEMS_PER_CU;
   sc.heads_per_group = heads_per_group(BH, sc.n_chunks * sc.n_psplit, group_items * cus);
   sc.n_groups = BH / sc.heads_per_group;
-  sc.lag = std::min(NACL_SCORE_LAG, sc.n_groups);
-  sc.total_items = passes * BH * sc.n_chunks * sc.n_psplit;
+  sc.lag = sc.fused ? sc.n_groups : std::min(NACL_SCORE_LAG, sc.n_groups);
+  sc.total_items = (sc.fused ? 1 : passes) * BH * sc.n_chunks * sc.n_psplit;
   sc.partials = reinterpret_cast<float2*>(ws + l.part);
   sc.lse2 = reinterpret_cast<float*>(ws + l.lse);
   sc.lse_in = lse;
   sc.lse_mul = 1.4426950408889634f;
-  if (!sc.lse_given && nacl::score_uses_rows(p->dtype, p->D, rows_of(p))) {
+  if (!sc.lse_given && nacl::score_uses_rows(p->dtype, p->D, rows)) {
     // Few proxy rows: K is read once and the logits are kept (see score.hip).
     sc.logits = reinterpret_cast<float*>(ws + l.logits);
     sc.logits_stride = logits_stride(p);

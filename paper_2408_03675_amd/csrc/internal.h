@@ -36,17 +36,17 @@ constexpr int kScoreTpwMin = 8;
 constexpr int kScoreTpwMax = NACL_SCORE_TPW_MAX;
 constexpr int kScoreWavesPerSimd = NACL_SCORE_WAVES;
 constexpr int kScoreWaves = 4;  // waves per work-group, each owning a quarter of the item's keys
-// Proxy-split variant (bf16, D = 128, at least 128 proxies): the waves of a
-// block share one ring of K tiles and split each group of 128 proxies, so an
-// item is kSplitChunkKeys keys.
-#ifndef NACL_SCORE_SPLIT
-#define NACL_SCORE_SPLIT 1
-#endif
+// Proxy-split variants (bf16, D = 128, 128 to kBlockRows proxy rows or at
+// least kSplitWideRows): the waves of a block share one ring of K tiles and
+// split the rows, so an item is kSplitChunkKeys keys.
 #ifndef NACL_SPLIT_CHUNK
 #define NACL_SPLIT_CHUNK 2048
 #endif
 constexpr int kSplitChunkKeys = NACL_SPLIT_CHUNK;
-inline bool score_uses_split(int dtype, int D, int P) { return NACL_SCORE_SPLIT && dtype == 1 && D == 128 && P >= 128; }
+constexpr int kSplitChunkMin = 512;  // shorter items where the heads are few or short
+constexpr int kSplitRows = 128;      // rows of the split kernel
+constexpr int kBlockRows = 256;      // most rows of the block kernel
+inline bool score_uses_split(int dtype, int D, int P) { return dtype == 1 && D == 128 && P >= kSplitRows; }
 // Proxy rows per group of the wide split kernel (from this many rows on it
 // is the one launched), and its items per chunk along the rows.
 constexpr int kSplitWideRows = 512;
@@ -70,6 +70,12 @@ int score_rows_chunk(int dtype, int D, int L, int BH, int cus);
 // for kRowsChunkMin-key chunks on the few-row path).
 constexpr int kScoreMinChunkKeys = std::min(kScoreTpwMin * kScoreWaves * 16, kSplitChunkKeys);
 
+// Keys-in-registers variant (bf16): 8 waves of 64 keys, one work-group per CU.
+constexpr int kKeysThreads = 512;
+constexpr int kKeysFuseMax = 512;  // most items of a launch whose passes share their keys
+constexpr int kKeysTwoMin = 64, kKeysTwoMax = 128;  // rows with which a work-group may take two of them (above, up to)
+enum ScorePath { kScoreTiles = 0, kScoreSplit = 1, kScoreKeys = 2 };
+
 struct ScoreArgs {
   int B, H, L, P;   // P: proxy rows per K/V head = P0 * qg, row r = proxy r / qg of query head r % qg
   int P0, qg;       // proxies, query heads per K/V head
@@ -91,6 +97,8 @@ struct ScoreSched {
   int n_psplit;          // items per chunk along the proxy rows: 1, or one per group of
                          // kSplitWideRows rows (long proxy lists; the column sums of a chunk
                          // are then added in group order by the chunk's last item)
+  int path;              // ScorePath (unless logits is set)
+  int fused;             // kScoreKeys: the items are pass 1 only, and each work-group follows with pass 2 of its own
   int lse_given;         // 1: the caller supplied the log-sum-exp, only pass 2 runs
   uint32_t* queue;       // workspace counter words: queue, status, then per-head counters
   uint32_t* status;      // health words: [0] this call's, [1] sticky; bit 0 set if a pass-2

@@ -24,10 +24,13 @@
 // memory-side cache does not serve that re-read faster than HBM on this part,
 // so K crosses HBM twice and the kernel is bound by 2 x |K| / HBM bandwidth.
 //
-// For bf16 inputs with D = 128 and at least 128 proxies, score_split_kernel
-// (below) replaces this layout: the waves of a block share the tile ring and
-// split the proxy group instead, which frees registers for four blocks per
-// CU.  Everything else (queue, passes, merge, reproducibility) is the same.
+// For bf16 inputs other layouts replace this one (below; the choice by rows
+// and items is run_score's): score_keys_kernel for small launches, whose work-
+// groups do both passes over keys they hold, and for 129 to 512 rows of D = 64
+// and 257 to 511 of D = 128; score_split_kernel (128 rows of D = 128) and
+// score_split_wide_kernel (512 and more), where the waves of a block share the
+// tile ring and split the proxy group; score_block_kernel (129 to 256 rows).
+// The queue, the passes, the merge and reproducibility are the same.
 //
 // Work-groups take items from a queue counter in a fixed order: the pass-1
 // items of head group g + lag come before the pass-2 items of head group g,
@@ -1004,11 +1007,8 @@ __global__ __launch_bounds__(kScoreThreads) void score_rows_column_kernel(ScoreA
 #ifndef NACL_SPLIT_OCC
 #define NACL_SPLIT_OCC 4
 #endif
-// Proxy lists at least this long use groups of 512 (eight blocks per wave).
-constexpr int kSplitWideP = kSplitWideRows;
 constexpr int kSplitDepth = NACL_SPLIT_DEPTH;                // ring slots per block (at most 8)
-constexpr int kSplitTiles = kSplitChunkKeys / 16;            // tiles per item
-static_assert(kSplitTiles % kSplitDepth == 0 && kSplitDepth % 4 == 0, "tiles per item vs ring");
+static_assert(kSplitChunkMin / 16 % kSplitDepth == 0 && kSplitDepth % 4 == 0, "tiles per item vs ring");
 
 __device__ __forceinline__ void block_barrier() {
   // A barrier without the full fence of __syncthreads(): it waits for this
@@ -1016,6 +1016,117 @@ __device__ __forceinline__ void block_barrier() {
   // after it) but not for its vector memory operations, so the DMA of later
   // tiles stays in flight across it.
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// After an item's partials are stored (store_coherent): counts the item in, and
+// the head's last one merges its n_chunks partials per row into the row's
+// log-sum-exp and publishes it with one more count.  Every thread calls it.
+template <int kT>
+__device__ __forceinline__ void publish_partials(const ScoreArgs& a, const ScoreSched& s, int bh, float2 (&mrg)[kT],
+                                                 int& last_s) {
+  wait_stores();
+  __syncthreads();
+  if (threadIdx.x == 0) last_s = atomicAdd(&s.head_cnt[bh], 1u) == (unsigned)(s.n_chunks * s.n_psplit - 1);
+  __syncthreads();
+  if (last_s) {
+    const float2* hp = s.partials + (int64_t)bh * s.n_chunks * a.P;
+    const int split = a.P >= kT ? 1 : kT / a.P;
+    const int part_i = threadIdx.x / a.P;
+    constexpr int kBatch = 8;
+    for (int i0 = 0; i0 < a.P; i0 += kT) {
+      const int i = i0 + (split == 1 ? (int)threadIdx.x : (int)threadIdx.x % a.P);
+      float mm = -INFINITY, ss = 0.f;
+      if (i < a.P && part_i < split) {
+        for (int c0 = part_i; c0 < s.n_chunks; c0 += kBatch * split) {
+          float2 v[kBatch];
+#pragma unroll
+          for (int u = 0; u < kBatch; ++u) {
+            const int c = c0 + u * split;
+            v[u] = c < s.n_chunks ? load_coherent(hp + (int64_t)c * a.P + i) : make_float2(-INFINITY, 0.f);
+          }
+#pragma unroll
+          for (int u = 0; u < kBatch; ++u) lse_merge(mm, ss, v[u].x, v[u].y);
+        }
+      }
+      if (split > 1) {
+        mrg[threadIdx.x] = make_float2(mm, ss);
+        __syncthreads();
+        if (part_i == 0 && i < a.P)
+          for (int pp = 1; pp < split; ++pp) {
+            const float2 r = mrg[threadIdx.x + pp * a.P];
+            lse_merge(mm, ss, r.x, r.y);
+          }
+      }
+      if (part_i == 0 && i < a.P) store_coherent(s.lse2 + (int64_t)bh * a.P + i, mm + __log2f(ss));
+    }
+    wait_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&s.head_cnt[bh], 1u);
+  }
+}
+
+// Waits (bounded) until the head's log-sum-exp is published.  Every thread calls it.
+__device__ __forceinline__ void wait_lse(const ScoreSched& s, int bh) {
+  if (threadIdx.x == 0) {
+    uint32_t spins = 0;
+    while (load_coherent(&s.head_cnt[bh]) < (unsigned)(s.n_chunks * s.n_psplit + 1)) {
+      __builtin_amdgcn_s_sleep(2);
+      if (++spins > kSpinLimit) {
+        atomicOr(s.status, 1u);
+        atomicOr(s.status + 1, 1u);
+        break;
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// The end of a pass-2 item whose column sums are in col_lds (fresh: none were
+// written): with items split along the rows the chunk's last one adds all of
+// them; then the scores and, inside a whole eviction, their Gumbel keys.
+template <int kT, class Keys>
+__device__ __forceinline__ void finish_columns(const ScoreArgs& a, const ScoreSched& s, const ItemRef& it, int bh,
+                                               int chunk_key0, bool fresh, int group, float* col_lds, int& last_s,
+                                               Keys&& chunk_gumbel_keys) {
+  __syncthreads();
+  bool write = true;
+  if (s.n_psplit > 1) {
+    // Publish this group's column sums (none if no row of it sees the
+    // chunk); the chunk's last item adds the groups' sums in group order,
+    // as one item over every group would, and writes the scores.
+    const int64_t cidx = (int64_t)bh * s.n_chunks + it.chunk;
+    float* cp = s.colpart + cidx * s.n_psplit * s.chunk_keys;
+    if (!fresh)
+      for (int q4 = 4 * (int)threadIdx.x; q4 < s.chunk_keys; q4 += 4 * kT)
+        store_coherent16(cp + it.psl * s.chunk_keys + q4,
+                         __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4*>(col_lds + q4)));
+    wait_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) last_s = atomicAdd(&s.chunk_cnt[cidx], 1u) == (unsigned)(s.n_psplit - 1);
+    __syncthreads();
+    write = last_s != 0;
+    if (write) {
+      for (int idx = threadIdx.x; idx < s.chunk_keys; idx += kT) {
+        float acc = 0.f;
+        for (int pg = 0; pg < s.n_psplit; ++pg) {
+          int64_t unused;
+          const int lr = min(a.P, (pg + 1) * group) - 1;  // the group's last row
+          if (row_position(a, lr, unused) >= chunk_key0) acc += load_coherent(cp + pg * s.chunk_keys + idx);
+        }
+        col_lds[idx] = acc;
+      }
+      __syncthreads();
+    }
+  }
+  if (write) {
+    float* F = s.scores + (int64_t)bh * a.L;
+    auto col_of = [&](int idx) -> float { return col_lds[idx]; };
+    for (int idx = threadIdx.x; idx < s.chunk_keys; idx += kT) {
+      const int key = chunk_key0 + idx;
+      if (key < a.L) F[key] = col_of(idx);
+    }
+    if (s.gkeys) chunk_gumbel_keys(col_of);
+  }
 }
 
 // WB proxy blocks of 16 per wave, so proxy groups of 64 * WB: WB = 2 (groups
@@ -1034,7 +1145,6 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
   constexpr int kSplitGroup = 16 * WB * kScoreWaves;  // proxies per group
   constexpr int kNB = WB < 4 ? WB : 4;                // proxy blocks per MFMA batch
   static_assert(KS::kInstr == kScoreWaves, "one DMA instruction per wave and tile");
-  static_assert(WB != 8 || kSplitGroup == kSplitWideRows, "row groups of split items are the wide kernel's groups");
   __shared__ int item_s, last_s;
   __shared__ int pos_g[kSplitGroup];
   __shared__ int64_t qrow_g[kSplitGroup];  // element offset of each row's query from qb
@@ -1059,6 +1169,7 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
   for (int i = 1; i < KS::kInstr; ++i) vo = wave == i ? vo_all[i] : vo;
   const uint32_t voff = (uint32_t)r16 * row_bytes + 16u * (uint32_t)g;  // direct fragment loads (exact path)
   const int w0 = 16 * WB * wave;  // this wave's first proxy within the group
+  const int n_tiles = s.chunk_keys / 16;
 
   for (;;) {
     __syncthreads();
@@ -1070,13 +1181,13 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
     const int bh = it.bh, b = bh / a.H, h = bh % a.H;
     const T* qb = q + b * a.qs[0] + (int64_t)h * a.qg * a.qs[1];  // first query head of the group
     const T* kb = k + b * a.ks[0] + h * a.ks[1];
-    const int chunk_key0 = it.chunk * kSplitChunkKeys;
+    const int chunk_key0 = it.chunk * s.chunk_keys;
     const bool beyond = chunk_key0 > a.p_last;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(kb), (short)0, (int)((uint32_t)(a.L - 1) * row_bytes + (uint32_t)(D * sizeof(T))),
         kBufferRsrcWord3);
     auto tile_byte = [&](int t) -> uint32_t {
-      return t < kSplitTiles ? (uint32_t)(chunk_key0 + 16 * t) * row_bytes : kOutOfRange;
+      return t < n_tiles ? (uint32_t)(chunk_key0 + 16 * t) * row_bytes : kOutOfRange;
     };
     auto slot = [&](auto u_c) -> unsigned char* {
       constexpr int u = decltype(u_c)::value % kSplitDepth;
@@ -1102,7 +1213,7 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
     auto k_tiles = [&](auto&& tile_fn) {
       static_for<kSplitDepth - 1>([&](auto u_c) { issue(decltype(u_c)::value, slot(u_c)); });
 #pragma unroll 1
-      for (int t = 0; t < kSplitTiles; t += kSplitDepth) {
+      for (int t = 0; t < n_tiles; t += kSplitDepth) {
         static_for<kSplitDepth>([&](auto u_c) {
           constexpr int u = decltype(u_c)::value;
           const int tt = t + u;
@@ -1136,7 +1247,7 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
     };
     auto chunk_gumbel_keys = [&](auto&& f_of) {
       uint32_t* gk = s.gkeys + (int64_t)bh * a.L;
-      for (int q4 = 4 * (int)threadIdx.x; q4 < kSplitChunkKeys; q4 += 4 * kScoreThreads) {
+      for (int q4 = 4 * (int)threadIdx.x; q4 < s.chunk_keys; q4 += 4 * kScoreThreads) {
         const int j0 = chunk_key0 + q4;
         if (j0 >= a.L) break;
         const int n = min(4, a.L - j0);
@@ -1237,7 +1348,7 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
           for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
             for (int pb = 0; pb < WB; ++pb) sm[pb] = 0.f;
-            for (int t = 0; t < kSplitTiles; ++t) {
+            for (int t = 0; t < n_tiles; ++t) {
               const int key0 = chunk_key0 + 16 * t;
               if (key0 > last) break;
               frag_t kf[kS];
@@ -1278,69 +1389,17 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
           }
         }
       }
-      // Publish the partials; the last chunk of the head merges them.
-      wait_stores();
-      __syncthreads();
-      if (threadIdx.x == 0) last_s = atomicAdd(&s.head_cnt[bh], 1u) == (unsigned)(s.n_chunks * s.n_psplit - 1);
-      __syncthreads();
-      if (last_s) {
-        const float2* hp = s.partials + (int64_t)bh * s.n_chunks * a.P;
-        const int split = a.P >= kScoreThreads ? 1 : kScoreThreads / a.P;
-        const int part_i = threadIdx.x / a.P;
-        constexpr int kBatch = 8;
-        for (int i0 = 0; i0 < a.P; i0 += kScoreThreads) {
-          const int i = i0 + (split == 1 ? (int)threadIdx.x : (int)threadIdx.x % a.P);
-          float mm = -INFINITY, ss = 0.f;
-          if (i < a.P && part_i < split) {
-            for (int c0 = part_i; c0 < s.n_chunks; c0 += kBatch * split) {
-              float2 v[kBatch];
-#pragma unroll
-              for (int u = 0; u < kBatch; ++u) {
-                const int c = c0 + u * split;
-                v[u] = c < s.n_chunks ? load_coherent(hp + (int64_t)c * a.P + i) : make_float2(-INFINITY, 0.f);
-              }
-#pragma unroll
-              for (int u = 0; u < kBatch; ++u) lse_merge(mm, ss, v[u].x, v[u].y);
-            }
-          }
-          if (split > 1) {
-            mrg[threadIdx.x] = make_float2(mm, ss);
-            __syncthreads();
-            if (part_i == 0 && i < a.P)
-              for (int pp = 1; pp < split; ++pp) {
-                const float2 r = mrg[threadIdx.x + pp * a.P];
-                lse_merge(mm, ss, r.x, r.y);
-              }
-          }
-          if (part_i == 0 && i < a.P) store_coherent(s.lse2 + (int64_t)bh * a.P + i, mm + __log2f(ss));
-        }
-        wait_stores();
-        __syncthreads();
-        if (threadIdx.x == 0) atomicAdd(&s.head_cnt[bh], 1u);
-      }
+      publish_partials<kScoreThreads>(a, s, bh, mrg, last_s);
     } else if (beyond) {
       if (it.psl == 0) {
         float* F = s.scores + (int64_t)bh * a.L;
-        const int end = min(chunk_key0 + kSplitChunkKeys, a.L);
+        const int end = min(chunk_key0 + s.chunk_keys, a.L);
         for (int j = chunk_key0 + threadIdx.x; j < end; j += kScoreThreads) F[j] = 0.f;
         if (s.gkeys) chunk_gumbel_keys([](int) { return 0.f; });
       }
     } else {
       // ---------------- pass 2: column sums of exp2(logit - LSE) ----------
-      if (!s.lse_given) {
-        if (threadIdx.x == 0) {
-          uint32_t spins = 0;
-          while (load_coherent(&s.head_cnt[bh]) < (unsigned)(s.n_chunks * s.n_psplit + 1)) {
-            __builtin_amdgcn_s_sleep(2);
-            if (++spins > kSpinLimit) {
-              atomicOr(s.status, 1u);
-              atomicOr(s.status + 1, 1u);
-              break;
-            }
-          }
-        }
-        __syncthreads();
-      }
+      if (!s.lse_given) wait_lse(s, bh);
       const float* lse = s.lse_given ? s.lse_in : s.lse2;
       const float lse_mul = s.lse_given ? s.lse_mul : 1.0f;
       bool fresh = true;  // the item's columns are not yet written
@@ -1425,48 +1484,828 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
           if constexpr (u % 4 == 3) stage[wave][lane] = colsum4(cs4[0], cs4[1], cs4[2], cs4[3]);
         });
         __syncthreads();
-        reduce_stage(kSplitTiles - 4);
+        reduce_stage(n_tiles - 4);
         fresh = false;
       }
+      finish_columns<kScoreThreads>(a, s, it, bh, chunk_key0, fresh, kSplitGroup, col_lds, last_s, chunk_gumbel_keys);
+    }
+  }
+}
+
+// A 32x32 tile holds, in lane (hl, n) with hl = lane / 32, column n and rows
+// 8 (i / 4) + 4 hl + i % 4 for i = 0 .. 15: keys of row n in pass 1, rows of
+// key n in pass 2.
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// Sum / maximum of the two lane halves.
+__device__ __forceinline__ float half_sum(float x) {
+  auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float half_max(float x) {
+  auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+// A value computed where it stands: the compiler does not move it to its use.
+__device__ __forceinline__ float here(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// Step c of 16 logits' vector work: logits 2 c and 2 c + 1 take their FMA,
+// 2 c - 2 and 2 c - 1 their exponential, and 2 c - 4 and 2 c - 3 are added.
+template <int c>
+__device__ __forceinline__ void vec_step(f32x16& v, float c2, float m0, float m1, float (&ps)[2]) {
+  if constexpr (c >= 2) {
+    ps[0] = c == 2 ? v[0] : here(ps[0] + v[2 * c - 4]);
+    ps[1] = c == 2 ? v[1] : here(ps[1] + v[2 * c - 3]);
+  }
+  if constexpr (c >= 1) {
+    v[2 * c - 2] = here(fast_exp2(v[2 * c - 2]));
+    v[2 * c - 1] = here(fast_exp2(v[2 * c - 1]));
+  }
+  v[2 * c] = here(fmaf(v[2 * c], c2, m0));
+  v[2 * c + 1] = here(fmaf(v[2 * c + 1], c2, m1));
+  if constexpr (c == 7) {
+    ps[0] = here(ps[0] + v[12]) + here(fast_exp2(v[14]));
+    ps[1] = here(ps[1] + v[13]) + here(fast_exp2(v[15]));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 129 to 256 proxy rows (bf16, D = 128): the contraction and K's stream weigh
+// about the same, so K is streamed once per pass for all rows, and matrix and
+// vector work stand side by side.  As in score_split_body the four waves of a
+// block share a ring of K tiles and split the rows, here 64 each (two blocks
+// of 32) and tiles of 32 keys (v_mfma_f32_32x32x16_bf16); a unit of eight
+// MFMAs (one block of one tile) carries the vector work of the unit before
+// it, two logits per MFMA, kept in place by sched_barriers.  Tiles that some
+// row of the wave does not see whole, and an item's first tile in pass 1 (it
+// sets the references), run unit after unit with masks.  score_split_body
+// would take two groups of 128 rows and stream K twice per pass: one layer of
+// 32 heads, 32k tokens and 256 rows 260 us, here 178; with the caller's
+// log-sum-exp 112 and 93.5; 16 heads of 12345 keys, 200 rows: 134 and 62.5.
+__device__ __forceinline__ void score_block_body(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
+                                                 const ScoreArgs& a, const ScoreSched& s) {
+  constexpr int NRB = 2;                              // row blocks per wave
+  constexpr int D = 128, kC = D / 16;                 // contraction steps
+  constexpr int kGroup = 32 * NRB * kScoreWaves;      // proxy rows per item
+  static_assert(kGroup == kBlockRows, "rows of the launch");
+  constexpr int kDepth = 4, kTileKeys = 32, kTileBytes = kTileKeys * D * 2;
+  constexpr int kDma = kTileBytes / 1024 / kScoreWaves;  // 1 KB loads per wave and tile
+  __shared__ int item_s, last_s;
+  __shared__ __attribute__((aligned(16))) int pos_g[kGroup];
+  __shared__ int64_t qrow_g[kGroup];  // element offset of each row's query from qb
+  __shared__ float2 mrg[kScoreThreads];
+  __shared__ __attribute__((aligned(16))) float col_lds[kSplitChunkKeys];
+  __shared__ float stage[kScoreWaves][64];
+  __shared__ __attribute__((aligned(16))) float lse_g[kGroup];
+#define NACL_BSLOT(i) __shared__ __attribute__((aligned(16))) unsigned char bslot##i[kTileBytes];
+  NACL_BSLOT(0) NACL_BSLOT(1) NACL_BSLOT(2) NACL_BSLOT(3)
+#undef NACL_BSLOT
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hl = lane >> 5, n32 = lane & 31;
+  const float c2 = a.c2;
+  const uint32_t row_bytes = (uint32_t)(a.ks[2] * (int64_t)sizeof(__bf16));
+  // This wave's loads of a tile: rows 4 i .. 4 i + 3 of load i, chunks
+  // XOR-swizzled by row (the rows of a fragment read hit distinct banks).
+  uint32_t vo[kDma];
+#pragma unroll
+  for (int i = 0; i < kDma; ++i) {
+    const int row = (wave * kDma + i) * 4 + lane / 16;
+    vo[i] = (uint32_t)row * row_bytes + (uint32_t)(((lane % 16) ^ (row & 15)) * 16);
+  }
+  uint32_t ka[kC];  // fragment c: row n32, chunk 2 c + hl
+#pragma unroll
+  for (int c = 0; c < kC; ++c) ka[c] = (uint32_t)(n32 * 256 + (((2 * c + hl) ^ (n32 & 15)) * 16));
+  const uint32_t voff = (uint32_t)n32 * row_bytes + 16u * (uint32_t)hl;  // direct fragment loads (exact path)
+  const int w0 = 32 * NRB * wave;  // this wave's first row
+  const int n_tiles = s.chunk_keys / kTileKeys;
+
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x == 0) item_s = (int)atomicAdd(s.queue, 1u);
+    __syncthreads();
+    const int item = __builtin_amdgcn_readfirstlane(item_s);
+    if (item >= s.total_items) break;
+    const ItemRef it = decode_item(s, item);
+    const int bh = it.bh, b = bh / a.H, h = bh % a.H;
+    const __bf16* qb = q + b * a.qs[0] + (int64_t)h * a.qg * a.qs[1];  // first query head of the group
+    const __bf16* kb = k + b * a.ks[0] + h * a.ks[1];
+    const int chunk_key0 = it.chunk * s.chunk_keys;
+    const bool beyond = chunk_key0 > a.p_last;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16*>(kb), (short)0, (int)((uint32_t)(a.L - 1) * row_bytes + (uint32_t)(D * sizeof(__bf16))),
+        kBufferRsrcWord3);
+    auto slot = [&](auto u_c) -> unsigned char* {
+      constexpr int u = decltype(u_c)::value % kDepth;
+      if constexpr (u == 0) return bslot0;
+      else if constexpr (u == 1) return bslot1;
+      else if constexpr (u == 2) return bslot2;
+      else return bslot3;
+    };
+    // Tiles past the item read nothing.
+    auto issue = [&](int t, unsigned char* dst) {
+      const uint32_t off = t < n_tiles ? (uint32_t)(chunk_key0 + kTileKeys * t) * row_bytes : kOutOfRange;
+#pragma unroll
+      for (int i = 0; i < kDma; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rsrc, (__attribute__((address_space(3))) void*)(dst + (wave * kDma + i) * 1024), 16, vo[i] + off, 0, 0,
+            kScoreKAux);
+    };
+    // Streams the item's tiles through the ring, as in score_split_body.
+    auto k_tiles = [&](auto&& tile_fn) {
+      static_for<kDepth - 1>([&](auto u_c) { issue(decltype(u_c)::value, slot(u_c)); });
+#pragma unroll 1
+      for (int t = 0; t < n_tiles; t += kDepth) {
+        static_for<kDepth>([&](auto u_c) {
+          constexpr int u = decltype(u_c)::value;
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kDma * (kDepth - 2)) : "memory");
+          block_barrier();
+          issue(t + u + kDepth - 1, slot(std::integral_constant<int, u + kDepth - 1>{}));
+          tile_fn(t + u, slot(u_c), u_c);
+        });
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    auto frags = [&](const unsigned char* tile, bf16x8 (&kf)[kC]) {
+#pragma unroll
+      for (int c = 0; c < kC; ++c) kf[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(tile + ka[c]));
+    };
+    auto load_rows = [&]() {
       __syncthreads();
-      bool write = true;
-      if (s.n_psplit > 1) {
-        // Publish this group's column sums (none if no row of it sees the
-        // chunk); the chunk's last item adds the groups' sums in group order,
-        // as one item over every group would, and writes the scores.
-        const int64_t cidx = (int64_t)bh * s.n_chunks + it.chunk;
-        float* cp = s.colpart + cidx * s.n_psplit * kSplitChunkKeys;
-        if (!fresh)
-          for (int q4 = 4 * (int)threadIdx.x; q4 < kSplitChunkKeys; q4 += 4 * kScoreThreads)
-            store_coherent16(cp + it.psl * kSplitChunkKeys + q4,
-                             __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4*>(col_lds + q4)));
-        wait_stores();
-        __syncthreads();
-        if (threadIdx.x == 0) last_s = atomicAdd(&s.chunk_cnt[cidx], 1u) == (unsigned)(s.n_psplit - 1);
-        __syncthreads();
-        write = last_s != 0;
-        if (write) {
-          for (int idx = threadIdx.x; idx < kSplitChunkKeys; idx += kScoreThreads) {
-            float acc = 0.f;
-            for (int pg = 0; pg < s.n_psplit; ++pg) {
-              int64_t unused;
-              const int lr = min(a.P, (pg + 1) * kSplitGroup) - 1;  // the group's last row
-              if (row_position(a, lr, unused) >= chunk_key0) acc += load_coherent(cp + pg * kSplitChunkKeys + idx);
-            }
-            col_lds[idx] = acc;
+      for (int i = threadIdx.x; i < kGroup; i += kScoreThreads) pos_g[i] = i < a.P ? row_position(a, i, qrow_g[i]) : -1;
+      __syncthreads();
+    };
+    // This wave's Q fragments (row 32 rb + n32, chunk 2 c + hl; zeros past
+    // the last row) and the positions of its first and last row (no row:
+    // first = INT_MAX, last = -1).
+    auto load_wave_q = [&](bf16x8 (&qf)[NRB][kC], int& first, int& last) {
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) {
+        const int i = w0 + 32 * rb + n32;
+        const u32x4* p = reinterpret_cast<const u32x4*>(qb + (i < a.P ? qrow_g[i] : 0) + 8 * hl);
+#pragma unroll
+        for (int c = 0; c < kC; ++c) qf[rb][c] = __builtin_bit_cast(bf16x8, i < a.P ? p[2 * c] : u32x4{0u, 0u, 0u, 0u});
+      }
+      const int wn = min(max(a.P - w0, 0), 32 * NRB);
+      first = wn > 0 ? pos_g[w0] : 0x7FFFFFFF;
+      last = wn > 0 ? pos_g[w0 + wn - 1] : -1;
+    };
+    auto logits = [&](const bf16x8& fa, const bf16x8& fb, const f32x16& acc, bool first) {
+      const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      return __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, first ? z : acc, 0, 0, 0);
+    };
+    auto chunk_gumbel_keys = [&](auto&& f_of) {
+      uint32_t* gk = s.gkeys + (int64_t)bh * a.L;
+      for (int q4 = 4 * (int)threadIdx.x; q4 < s.chunk_keys; q4 += 4 * kScoreThreads) {
+        const int j0 = chunk_key0 + q4;
+        if (j0 >= a.L) break;
+        const int n = min(4, a.L - j0);
+        float fv[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < n; ++e) fv[e] = f_of(q4 + e);
+        uint32_t kv[4];
+        gumbel_block_keys(s.g_mode, j0, n, b, h, s.g_layer, s.g_k0, s.g_k1, fv, kv);
+        for (int e = 0; e < n; ++e) gk[j0 + e] = kv[e];
+      }
+    };
+    // One tile of a wave that sees it whole: the MFMAs of its units, each
+    // beside two logits' vector work of the unit before (none is pending at
+    // the first such tile); the last unit stays pending.
+    f32x16 sx[2];  // logits of the pending unit and the one being computed, by parity
+    auto whole_tile = [&](bool pending, const bf16x8 (&kf)[kC], auto&& mma, auto&& vec) {
+      static_for<NRB>([&](auto rb_c) {
+        constexpr int rb = decltype(rb_c)::value;
+        using Prev = std::integral_constant<int, 1 - rb>;  // the pending unit's block and parity
+        if (rb > 0 || pending) {
+          static_for<kC>([&](auto c_c) {
+            constexpr int c = decltype(c_c)::value;
+            sx[rb] = mma(kf[c], rb_c, c_c, sx[rb]);
+            vec(Prev{}, c_c);
+            __builtin_amdgcn_sched_barrier(0);
+          });
+        } else {
+          static_for<kC>([&](auto c_c) { sx[rb] = mma(kf[decltype(c_c)::value], rb_c, c_c, sx[rb]); });
+        }
+      });
+    };
+    using Last = std::integral_constant<int, NRB - 1>;
+
+    if (beyond) {  // no row sees the chunk
+      if (it.kind == 1) {
+        for (int i = threadIdx.x; i < a.P; i += kScoreThreads)
+          store_coherent(s.partials + ((int64_t)bh * s.n_chunks + it.chunk) * a.P + i, make_float2(-INFINITY, 0.f));
+        publish_partials<kScoreThreads>(a, s, bh, mrg, last_s);
+      } else {
+        float* F = s.scores + (int64_t)bh * a.L;
+        const int end = min(chunk_key0 + s.chunk_keys, a.L);
+        for (int j = chunk_key0 + threadIdx.x; j < end; j += kScoreThreads) F[j] = 0.f;
+        if (s.gkeys) chunk_gumbel_keys([](int) { return 0.f; });
+      }
+    } else if (it.kind == 1) {
+      // ---------------- pass 1: per-chunk (reference, sum) of every proxy row
+      float2* part = s.partials + ((int64_t)bh * s.n_chunks + it.chunk) * a.P;
+      load_rows();
+      bf16x8 qf[NRB][kC];
+      int first, last;
+      load_wave_q(qf, first, last);
+      // Per block: base-2 reference of this lane's row (the scaled maximum
+      // of the item's first tile, 0 if that shows the row nothing) and the
+      // running sum of exp2(logit * c2 - ref) over this lane's keys.
+      float ref[NRB], sm[NRB];
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) ref[rb] = sm[rb] = 0.f;
+      auto mma1 = [&](const bf16x8& kf, auto rb_c, auto c_c, const f32x16& acc) {
+        return logits(kf, qf[decltype(rb_c)::value][decltype(c_c)::value], acc, decltype(c_c)::value == 0);
+      };
+      float ps[2];
+      auto vec1 = [&](auto rb_c, auto c_c) {
+        constexpr int rb = decltype(rb_c)::value, c = decltype(c_c)::value;
+        vec_step<c>(sx[rb], c2, -ref[rb], -ref[rb], ps);
+        if constexpr (c == kC - 1) sm[rb] += ps[0] + ps[1];
+      };
+      auto flush1 = [&]() {  // the last unit of the tile before
+        static_for<kC>([&](auto c_c) { vec1(Last{}, c_c); });
+      };
+      bool pending = false;
+      k_tiles([&](int t, const unsigned char* tile, auto) {
+        const int key0 = chunk_key0 + kTileKeys * t;
+        bf16x8 kf[kC];
+        if (t > 0 && key0 <= last && key0 + kTileKeys - 1 <= first) {
+          frags(tile, kf);
+          whole_tile(pending, kf, mma1, vec1);
+          pending = true;
+          return;
+        }
+        if (pending) flush1();
+        pending = false;
+        if (key0 > last) return;  // no row of the wave sees the tile
+        frags(tile, kf);
+        static_for<NRB>([&](auto rb_c) {
+          constexpr int rb = decltype(rb_c)::value;
+          f32x16 v;
+          static_for<kC>([&](auto c_c) { v = mma1(kf[decltype(c_c)::value], rb_c, c_c, v); });
+          // key 8 (i / 4) + i % 4 of the lane half is visible up to lim
+          const int lim = opaque(pos_g[w0 + 32 * rb + n32] - key0 - 4 * hl);
+          if (t == 0) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mx = 8 * (i / 4) + i % 4 <= lim ? fmaxf(mx, v[i]) : mx;
+            mx = half_max(mx);
+            ref[rb] = mx != -INFINITY ? mx * c2 : 0.f;
           }
+          float y = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const float e = fast_exp2(fmaf(v[i], c2, -ref[rb]));
+            y += 8 * (i / 4) + i % 4 <= lim ? e : 0.f;
+          }
+          sm[rb] += y;
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      });
+      if (pending) flush1();
+      bool bad = false;
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) {
+        sm[rb] = half_sum(sm[rb]);
+        bad |= !(sm[rb] <= 3.0e38f);
+      }
+      if (__builtin_amdgcn_ballot_w64(bad)) {
+        // A key far above the first tile's maximum (this wave only): the
+        // maximum over every visible key, then the sums, with direct loads.
+        float mx[NRB];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) mx[rb] = -INFINITY;
+        for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+          for (int rb = 0; rb < NRB; ++rb) sm[rb] = 0.f;
+          for (int t = 0; t < n_tiles; ++t) {
+            const int key0 = chunk_key0 + kTileKeys * t;
+            if (key0 > last) break;
+            bf16x8 kf[kC];
+#pragma unroll
+            for (int c = 0; c < kC; ++c)
+              kf[c] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                     rsrc, voff + (uint32_t)key0 * row_bytes + 32u * c, 0, kScoreKAux));
+            static_for<NRB>([&](auto rb_c) {
+              constexpr int rb = decltype(rb_c)::value;
+              f32x16 v;
+              static_for<kC>([&](auto c_c) { v = mma1(kf[decltype(c_c)::value], rb_c, c_c, v); });
+              const int lim = pos_g[w0 + 32 * rb + n32] - key0 - 4 * hl;
+#pragma unroll
+              for (int i = 0; i < 16; ++i) {
+                const bool vis = 8 * (i / 4) + i % 4 <= lim;
+                if (pass == 0) mx[rb] = vis ? fmaxf(mx[rb], v[i]) : mx[rb];
+                else sm[rb] += vis ? fast_exp2(fmaf(v[i], c2, -ref[rb])) : 0.f;
+              }
+            });
+          }
+          if (pass == 0) {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) {
+              mx[rb] = half_max(mx[rb]);
+              ref[rb] = mx[rb] != -INFINITY ? mx[rb] * c2 : 0.f;
+            }
+          }
+        }
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) sm[rb] = half_sum(sm[rb]);
+      }
+      if (hl == 0) {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+          const int i = w0 + 32 * rb + n32;
+          if (i < a.P)
+            store_coherent(part + i, sm[rb] > 0.f ? make_float2(ref[rb], sm[rb]) : make_float2(-INFINITY, 0.f));
+        }
+      }
+      publish_partials<kScoreThreads>(a, s, bh, mrg, last_s);
+    } else {
+      // ---------------- pass 2: column sums of exp2(logit - LSE) ----------
+      if (!s.lse_given) wait_lse(s, bh);
+      const float* lse = s.lse_given ? s.lse_in : s.lse2;
+      const float lse_mul = s.lse_given ? s.lse_mul : 1.0f;
+      load_rows();
+      bf16x8 qf[NRB][kC];
+      int first, last;
+      load_wave_q(qf, first, last);
+      for (int i = threadIdx.x; i < kGroup; i += kScoreThreads)
+        lse_g[i] = i < a.P ? load_coherent(lse + lse_index(a, s, bh, i)) * lse_mul : INFINITY;
+      __syncthreads();
+      // This lane's rows 32 rb + 8 (i / 4) + 4 hl + i % 4.
+      const int* pos_l = pos_g + w0 + 4 * hl;
+      f32x4 lr[NRB][4];
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lr[rb][i] = *reinterpret_cast<const f32x4*>(lse_g + w0 + 4 * hl + 32 * rb + 8 * i);
+      auto mma2 = [&](const bf16x8& kf, auto rb_c, auto c_c, const f32x16& acc) {
+        return logits(qf[decltype(rb_c)::value][decltype(c_c)::value], kf, acc, decltype(c_c)::value == 0);
+      };
+      float ps[2], cs = 0.f, done = 0.f;  // cs: the tile in hand; done: the tile before
+      auto vec2 = [&](auto rb_c, auto c_c) {
+        constexpr int rb = decltype(rb_c)::value, c = decltype(c_c)::value;
+        vec_step<c>(sx[rb], c2, -lr[rb][c / 2][2 * (c % 2)], -lr[rb][c / 2][2 * (c % 2) + 1], ps);
+        if constexpr (c == kC - 1) {
+          cs += ps[0] + ps[1];
+          if constexpr (rb == NRB - 1) {
+            done = cs;
+            cs = 0.f;
+          }
+        }
+      };
+      auto flush2 = [&]() { static_for<kC>([&](auto c_c) { vec2(Last{}, c_c); }); };
+      // Column sums by tile: a tile's is complete one step later.  Tiles
+      // 2 m and 2 m + 1 are reduced over the lane halves and staged per
+      // wave; wave 0 adds the four waves' stages in order a step later.
+      float even = 0.f;
+      auto put_stage = [&](float odd) {
+        auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(even), __float_as_uint(odd), false, false);
+        stage[wave][lane] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+      };
+      auto reduce_stage = [&](int t0) {  // tiles t0 and t0 + 1
+        if (wave == 0)
+          col_lds[t0 * kTileKeys + lane] = ((stage[0][lane] + stage[1][lane]) + stage[2][lane]) + stage[3][lane];
+      };
+      bool pending = false;
+      k_tiles([&](int t, const unsigned char* tile, auto u_c) {
+        constexpr int u = decltype(u_c)::value;
+        const int key0 = chunk_key0 + kTileKeys * t;
+        bf16x8 kf[kC];
+        if constexpr (u % 2 == 1) {
+          if (t >= 3) reduce_stage(t - 3);  // staged in the step before
+        }
+        if (!pending) {
+          done = cs;  // the masked tile before this one
+          cs = 0.f;
+        }
+        if (key0 <= last && key0 + kTileKeys - 1 <= first) {
+          frags(tile, kf);
+          whole_tile(pending, kf, mma2, vec2);
+          pending = true;
+        } else {
+          if (pending) flush2();
+          pending = false;
+          if (key0 <= last) {
+            frags(tile, kf);
+            static_for<NRB>([&](auto rb_c) {
+              constexpr int rb = decltype(rb_c)::value;
+              f32x16 v;
+              static_for<kC>([&](auto c_c) { v = mma2(kf[decltype(c_c)::value], rb_c, c_c, v); });
+              float y = 0.f;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const i32x4 pl = *reinterpret_cast<const i32x4*>(pos_l + opaque(32 * rb + 8 * i));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const float z = fast_exp2(fmaf(v[4 * i + e], c2, -lr[rb][i][e]));
+                  y += key0 + n32 <= pl[e] ? z : 0.f;
+                }
+                __builtin_amdgcn_sched_barrier(0);  // four rows at a time: few registers
+              }
+              cs += y;
+            });
+          }
+        }
+        // done: tile t - 1's column sum.
+        if constexpr (u % 2 == 1) even = done;  // tile t - 1 is even
+        else if (t > 0) put_stage(done);        // tile t - 1 is odd
+      });
+      if (pending) flush2();
+      else done = cs;
+      __syncthreads();  // the stage of tiles n - 4, n - 3 was added in the last step
+      put_stage(done);
+      __syncthreads();
+      reduce_stage(n_tiles - 2);
+      finish_columns<kScoreThreads>(a, s, it, bh, chunk_key0, false, kGroup, col_lds, last_s, chunk_gumbel_keys);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Keys in registers (bf16): launches that K's stream does not bound, which are
+// those of many proxy rows (the contraction outweighs K's bytes) and those
+// too small to fill the chip.  In score_split_body a tile's step ends in a
+// barrier of the work-group, and a wave's exponentials follow its logits;
+// here the proxy rows sit in LDS (up to 512 of them) and each of eight waves
+// holds 64 keys in registers and walks down the rows by itself: no barrier,
+// no ring, and the MFMAs of 32 rows (v_mfma_f32_32x32x16_bf16) stand beside
+// the vector work of the 32 rows before, kept in place by sched_barriers.
+// When a pass has no more items than work-groups (one of 512 keys each), the
+// work-group that did a chunk's first pass does its second one too, with the
+// keys and rows it already holds: K crosses HBM once, and what is left is the
+// chain of loading, first pass, log-sum-exp and second pass.  32 heads of
+// 4096 keys, 64 rows: 39.0 us by tiles, here 29.8; 6 heads of 32k keys, 400
+// rows: 258 in groups of 128, here 85.
+
+// FUSED: the items are pass 1 only, and pass 2 of a work-group's items follows.
+template <int D, int NRB, bool FUSED>
+__device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
+                                                const ScoreArgs& a, const ScoreSched& s) {
+  constexpr int kT = kKeysThreads, kWv = kT / 64;
+  constexpr int kC = D / 16;                       // contraction steps
+  constexpr int kGroup = 32 * NRB;                 // most proxy rows of an item
+  constexpr int kRowB = D * 2, kChunksRow = kRowB / 16, kSwz = kChunksRow - 1;
+  __shared__ int item_s, last_s;
+  __shared__ __attribute__((aligned(16))) int pos_g[kGroup];
+  __shared__ __attribute__((aligned(16))) float lse_g[kGroup];
+  // Pass 1: the waves' (reference, sum) of 256 rows, then the merge of a
+  // head's partials; pass 2: the item's column sums.
+  constexpr int kHalf = NRB < 8 ? NRB : 8;
+  __shared__ __attribute__((aligned(16))) float2 red[std::max(kWv * 32 * kHalf, kSplitChunkKeys / 2)];
+  float2(&mrg)[kT] = *reinterpret_cast<float2(*)[kT]>(red);
+  float* col_lds = reinterpret_cast<float*>(red);
+  __shared__ uint16_t done_l[FUSED ? kKeysFuseMax : 1];  // the items whose first pass ran here
+  __shared__ __attribute__((aligned(16))) unsigned char q_lds[kGroup * kRowB];  // rows, 16-byte chunks XOR-swizzled
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hl = lane >> 5, n32 = lane & 31;
+  const float c2 = a.c2;
+  const uint32_t row_bytes = (uint32_t)(a.ks[2] * (int64_t)sizeof(__bf16));
+  uint32_t qa[kC];  // fragment c of rows 32 rb + n32: chunk 2 c + hl
+#pragma unroll
+  for (int c = 0; c < kC; ++c) qa[c] = (uint32_t)(n32 * kRowB + (((2 * c + hl) ^ (n32 & kSwz)) * 16));
+  const int n_blocks = FUSED ? 1 : s.chunk_keys / (64 * kWv);  // 64-key blocks per wave and item
+
+  typedef bf16x8 Keys[2][kC];  // a wave's 64 keys: block kb, key n32, chunk 2 c + hl
+  bf16x8 qf[kC];      // the rows in hand, reloaded with the next ones as they are used
+  f32x16 sx[2][2];    // logits [parity][kb] of the rows before and the rows in hand
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  auto load_keys = [&](const __amdgpu_buffer_rsrc_t& rsrc, int key0, Keys& kf) {
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int c = 0; c < kC; ++c)
+        kf[kb][c] = __builtin_bit_cast(
+            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                        rsrc, (uint32_t)(key0 + 32 * kb + n32) * row_bytes + (uint32_t)(32 * c + 16 * hl), 0, 0));
+  };
+  auto row_frag = [&](int rb, int c) {
+    qf[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(q_lds + (qa[c] + (uint32_t)(rb * 32 * kRowB))));
+  };
+  // The logits of rows 32 rb .. + 31 into sx[par] (PASS 1: rows = keys; 2:
+  // rows = proxy rows), qf refilled with the rows of block next, beside(kb, c)
+  // for c = 0 .. 7 spread over the MFMAs.
+  auto unit = [&](auto pass_c, auto par_c, const Keys& kf, int next, auto&& beside) {
+    static_for<kC>([&](auto c_c) {
+      constexpr int c = decltype(c_c)::value;
+      static_for<2>([&](auto kb_c) {
+        constexpr int kb = decltype(kb_c)::value;
+        f32x16& v = sx[decltype(par_c)::value][kb];
+        const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if constexpr (decltype(pass_c)::value == 1)
+          v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][c], qf[c], c == 0 ? z : v, 0, 0, 0);
+        else
+          v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[c], kf[kb][c], c == 0 ? z : v, 0, 0, 0);
+        if constexpr (kb == 1) row_frag(next, c);
+        static_for<8 * (c + 1) / kC, 8 * c / kC>([&](auto e_c) { beside(kb_c, e_c); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  };
+  // No rows before the first: logits whose exponentials are zero.
+  auto clear_pending = [&]() {
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sx[1][kb][i] = -INFINITY;
+  };
+
+  int b = 0, h = 0, bh = 0, chunk_key0 = 0, gn = 0, nrb = 0;
+  const __bf16 *qb = nullptr, *kb_p = nullptr;
+  auto open = [&](const ItemRef& it) {
+    bh = it.bh, b = bh / a.H, h = bh % a.H;
+    qb = q + b * a.qs[0] + (int64_t)h * a.qg * a.qs[1];  // first query head of the group
+    kb_p = k + b * a.ks[0] + h * a.ks[1];
+    chunk_key0 = it.chunk * s.chunk_keys;
+    gn = a.P;
+    nrb = (gn + 31) / 32;
+  };
+  auto keys_rsrc = [&]() {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(kb_p), (short)0,
+                                             (int)((uint32_t)(a.L - 1) * row_bytes + (uint32_t)(D * sizeof(__bf16))),
+                                             kBufferRsrcWord3);
+  };
+  // The item's rows into LDS (zeros up to a multiple of 32), their positions
+  // (-1 past the last).  Every thread calls it; ends in a barrier.
+  auto load_rows = [&]() {
+    __syncthreads();
+    for (int i = threadIdx.x; i < kGroup; i += kT) {
+      int64_t unused;
+      pos_g[i] = i < gn ? row_position(a, i, unused) : -1;
+    }
+    __syncthreads();
+    constexpr int kBatch = 8;  // loads in flight per thread
+    const int n = nrb * 32 * kChunksRow;
+    for (int u0 = threadIdx.x; u0 < n; u0 += kBatch * kT) {
+      u32x4 w[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int r = (u0 + i * kT) / kChunksRow, x = (u0 + i * kT) % kChunksRow;
+        w[i] = u32x4{0u, 0u, 0u, 0u};
+        if (r < gn)
+          w[i] = *reinterpret_cast<const u32x4*>(qb + (int64_t)(r % a.qg) * a.qs[1] + (int64_t)pos_g[r] * a.qs[2] + 8 * x);
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int r = (u0 + i * kT) / kChunksRow, x = (u0 + i * kT) % kChunksRow;
+        if (u0 + i * kT < n) *reinterpret_cast<u32x4*>(q_lds + r * kRowB + ((x ^ (r & kSwz)) * 16)) = w[i];
+      }
+    }
+    __syncthreads();
+  };
+  // Blocks of rows with a row that does not see all 64 keys from key0 (the
+  // rows are sorted by position, so these are the first ones).
+  auto masked_rows = [&](int key0) {
+    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < nrb && pos_g[32 * min(lane, NRB - 1)] < key0 + 63));
+  };
+  auto block_key = [&](int j) { return chunk_key0 + (j * kWv + wave) * 64; };
+
+  // ---------------- pass 1: (reference, sum) of every row over the chunk ----
+  // FUSED leaves the keys in held.  A wave takes each row's maximum over
+  // its 64 keys, so no exponential exceeds 1; thread i merges row i over the
+  // waves and blocks, 256 rows at a time.
+  auto first_pass = [&](Keys& held) {
+    float2 mine = make_float2(-INFINITY, 0.f);
+    if (chunk_key0 <= pos_g[gn - 1]) {
+      const __amdgpu_buffer_rsrc_t rsrc = keys_rsrc();
+#pragma unroll 1
+      for (int j = 0; j < n_blocks; ++j) {
+        const int key0 = block_key(j);
+        const bool seen = key0 <= pos_g[gn - 1];
+        const int masked = masked_rows(key0);
+        Keys here_only;
+        Keys& kf = FUSED ? held : here_only;
+        if (seen) {
+          load_keys(rsrc, key0, kf);
+#pragma unroll
+          for (int c = 0; c < kC; ++c) row_frag(0, c);
+        }
+#pragma unroll 1
+        for (int r0 = 0; r0 < nrb; r0 += kHalf) {
+          const int r1 = min(r0 + kHalf, nrb);
+          float2* my_red = red + wave * (32 * kHalf);
+          if (seen) {
+            float ref[2] = {0.f, 0.f}, ps[2][2];
+            auto beside = [&](auto par_c) {
+              return [&, par_c](auto kb_c, auto e_c) {
+                constexpr int kb = decltype(kb_c)::value, e = decltype(e_c)::value, par = decltype(par_c)::value;
+                vec_step<e>(sx[par][kb], c2, -ref[par], -ref[par], ps[kb]);
+              };
+            };
+            // After the MFMAs of rows 32 rb ..: masks where some row does not
+            // see all 64 keys, then the lane's row's maximum.
+            auto settle = [&](auto par_c, int rb) {
+              constexpr int par = decltype(par_c)::value;
+              if (rb < masked) {
+                const int lim = pos_g[32 * rb + n32] - key0 - 4 * hl;  // key 32 kb + 8 (i / 4) + i % 4 is visible up to lim
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                  for (int i = 0; i < 16; ++i)
+                    if (32 * kb + 8 * (i / 4) + i % 4 > lim) sx[par][kb][i] = -INFINITY;
+              }
+              float x = -INFINITY, y = -INFINITY;
+#pragma unroll
+              for (int i = 0; i < 16; i += 2) {
+                x = fmaxf(fmaxf(x, sx[par][0][i]), sx[par][0][i + 1]);
+                y = fmaxf(fmaxf(y, sx[par][1][i]), sx[par][1][i + 1]);
+              }
+              x = half_max(fmaxf(x, y));
+              ref[par] = x != -INFINITY ? x * c2 : 0.f;
+            };
+            auto finish = [&](auto par_c, int rb) {
+              const float t = half_sum((ps[0][0] + ps[0][1]) + (ps[1][0] + ps[1][1]));
+              if (hl == 0)
+                my_red[32 * (rb - r0) + n32] = t > 0.f ? make_float2(ref[decltype(par_c)::value], t) : make_float2(-INFINITY, 0.f);
+            };
+            auto flush = [&](auto par_c) {
+              static_for<8>([&](auto e_c) {
+                beside(par_c)(C0{}, e_c);
+                beside(par_c)(C1{}, e_c);
+              });
+            };
+            clear_pending();
+#pragma unroll 1
+            for (int rb = r0; rb < r1; rb += 2) {
+              unit(C1{}, C0{}, kf, rb + 1 < nrb ? rb + 1 : 0, beside(C1{}));
+              if (rb > r0) finish(C1{}, rb - 1);
+              settle(C0{}, rb);
+              if (rb + 1 < r1) {
+                unit(C1{}, C1{}, kf, rb + 2 < nrb ? rb + 2 : 0, beside(C0{}));
+                finish(C0{}, rb);
+                settle(C1{}, rb + 1);
+              } else {
+                flush(C0{});
+                finish(C0{}, rb);
+              }
+            }
+            if ((r1 - r0) % 2 == 0) {
+              flush(C1{});
+              finish(C1{}, r1 - 1);
+            }
+          } else {
+            for (int i = lane; i < 32 * (r1 - r0); i += 64) my_red[i] = make_float2(-INFINITY, 0.f);
+          }
+          __syncthreads();
+          const int i = (int)threadIdx.x - 32 * r0;
+          if (i >= 0 && i < 32 * (r1 - r0))
+#pragma unroll
+            for (int w = 0; w < kWv; ++w) {
+              const float2 v = red[w * (32 * kHalf) + i];
+              lse_merge(mine.x, mine.y, v.x, v.y);
+            }
           __syncthreads();
         }
       }
-      if (write) {
-        float* F = s.scores + (int64_t)bh * a.L;
-        auto col_of = [&](int idx) -> float { return col_lds[idx]; };
-        for (int idx = threadIdx.x; idx < kSplitChunkKeys; idx += kScoreThreads) {
-          const int key = chunk_key0 + idx;
-          if (key < a.L) F[key] = col_of(idx);
-        }
-        if (s.gkeys) chunk_gumbel_keys(col_of);
+    }
+    if ((int)threadIdx.x < gn)
+      store_coherent(s.partials + ((int64_t)bh * s.n_chunks + chunk_key0 / s.chunk_keys) * a.P + threadIdx.x, mine);
+    publish_partials<kT>(a, s, bh, mrg, last_s);
+  };
+
+  // ---------------- pass 2: column sums of exp2(logit - LSE) ----------------
+  // IN_HAND: held has the (only) block's keys.
+  auto second_pass = [&](const ItemRef& it, auto in_hand, Keys& held) {
+    auto chunk_gumbel_keys = [&](auto&& f_of) {
+      uint32_t* gk = s.gkeys + (int64_t)bh * a.L;
+      for (int q4 = 4 * (int)threadIdx.x; q4 < s.chunk_keys; q4 += 4 * kT) {
+        const int j0 = chunk_key0 + q4;
+        if (j0 >= a.L) break;
+        const int n = min(4, a.L - j0);
+        float fv[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < n; ++e) fv[e] = f_of(q4 + e);
+        uint32_t kv[4];
+        gumbel_block_keys(s.g_mode, j0, n, b, h, s.g_layer, s.g_k0, s.g_k1, fv, kv);
+        for (int e = 0; e < n; ++e) gk[j0 + e] = kv[e];
       }
+    };
+    if (chunk_key0 > a.p_last) {  // no row sees the chunk
+      float* F = s.scores + (int64_t)bh * a.L;
+      const int end = min(chunk_key0 + s.chunk_keys, a.L);
+      for (int j = chunk_key0 + threadIdx.x; j < end; j += kT) F[j] = 0.f;
+      if (s.gkeys) chunk_gumbel_keys([](int) { return 0.f; });
+      return;
+    }
+    if (!s.lse_given) wait_lse(s, bh);
+    const bool fresh = chunk_key0 > pos_g[gn - 1];  // no row of the group sees the chunk
+    if (!fresh) {
+      const float* lse = s.lse_given ? s.lse_in : s.lse2;
+      const float lse_mul = s.lse_given ? s.lse_mul : 1.0f;
+      for (int i = threadIdx.x; i < kGroup; i += kT)
+        lse_g[i] = i < gn ? load_coherent(lse + lse_index(a, s, bh, i)) * lse_mul : INFINITY;
+      __syncthreads();
+      const __amdgpu_buffer_rsrc_t rsrc = keys_rsrc();
+      const float* lse_l = lse_g + 4 * hl;  // rows 8 (i / 4) + i % 4 of the lane half
+#pragma unroll 1
+      for (int j = 0; j < n_blocks; ++j) {
+        const int key0 = block_key(j);
+        float cs[2] = {0.f, 0.f}, ps[2][2];
+        if (key0 <= pos_g[gn - 1]) {
+          const int masked = masked_rows(key0);
+          Keys here_only;
+          Keys& kf = decltype(in_hand)::value ? held : here_only;
+          if constexpr (!decltype(in_hand)::value) load_keys(rsrc, key0, kf);
+#pragma unroll
+          for (int c = 0; c < kC; ++c) row_frag(0, c);
+          // Log-sum-exps of the pending rows, four for steps 2 i and 2 i + 1;
+          // those of the next rows are read once used.
+          f32x4 lr[4] = {};
+          const float* lse_n = lse_l;
+          auto beside = [&](auto par_c) {
+            return [&, par_c](auto kb_c, auto e_c) {
+              constexpr int kb = decltype(kb_c)::value, e = decltype(e_c)::value, i = e / 2;
+              vec_step<e>(sx[decltype(par_c)::value][kb], c2, -lr[i][2 * (e % 2)], -lr[i][2 * (e % 2) + 1], ps[kb]);
+              if constexpr (kb == 1 && e % 2 == 1) lr[i] = *reinterpret_cast<const f32x4*>(lse_n + 8 * i);
+              if constexpr (e == 7) cs[kb] += ps[kb][0] + ps[kb][1];
+            };
+          };
+          auto settle = [&](auto par_c, int rb) {
+            if (rb < masked) {
+              const int* pl = pos_g + 32 * rb + 4 * hl;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const i32x4 p = *reinterpret_cast<const i32x4*>(pl + 8 * i);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                  for (int e = 0; e < 4; ++e)
+                    if (key0 + 32 * kb + n32 > p[e]) sx[decltype(par_c)::value][kb][4 * i + e] = -INFINITY;
+              }
+            }
+          };
+          clear_pending();
+#pragma unroll 1
+          for (int rb = 0; rb < nrb; rb += 2) {
+            lse_n = lse_l + 32 * rb;
+            unit(std::integral_constant<int, 2>{}, C0{}, kf, rb + 1 < nrb ? rb + 1 : 0, beside(C1{}));
+            settle(C0{}, rb);
+            if (rb + 1 < nrb) {
+              lse_n = lse_l + 32 * rb + 32;
+              unit(std::integral_constant<int, 2>{}, C1{}, kf, rb + 2 < nrb ? rb + 2 : 0, beside(C0{}));
+              settle(C1{}, rb + 1);
+            } else {
+              static_for<8>([&](auto e_c) {
+                beside(C0{})(C0{}, e_c);
+                beside(C0{})(C1{}, e_c);
+              });
+            }
+          }
+          if (nrb % 2 == 0)
+            static_for<8>([&](auto e_c) {
+              beside(C1{})(C0{}, e_c);
+              beside(C1{})(C1{}, e_c);
+            });
+        }
+        auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(cs[0]), __float_as_uint(cs[1]), false, false);
+        col_lds[(j * kWv + wave) * 64 + lane] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+      }
+    }
+    finish_columns<kT>(a, s, it, bh, chunk_key0, fresh, kGroup, col_lds, last_s, chunk_gumbel_keys);
+  };
+
+  auto take = [&]() {
+    __syncthreads();
+    if (threadIdx.x == 0) item_s = (int)atomicAdd(s.queue, 1u);
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(item_s);
+  };
+  Keys held;
+  if constexpr (FUSED) {
+    int n = 0;
+    ItemRef it{};
+    for (int item = take(); item < s.total_items; item = take()) {
+      it = decode_item(s, item);
+      open(it);
+      load_rows();
+      first_pass(held);
+      if (threadIdx.x == 0) done_l[n] = (uint16_t)item;
+      ++n;
+    }
+    // No first pass is left: each is done or running, so every wait ends.
+    // The last item's keys and rows are still here; the others (there are
+    // some only if not every work-group found a CU) are read again.
+    if (n == 0) return;
+    second_pass(it, std::true_type{}, held);
+    for (int i = n - 2; i >= 0; --i) {
+      it = decode_item(s, done_l[i]);
+      open(it);
+      load_rows();
+      second_pass(it, std::false_type{}, held);
+    }
+  } else {
+    for (int item = take(); item < s.total_items; item = take()) {
+      const ItemRef it = decode_item(s, item);
+      open(it);
+      load_rows();
+      if (it.kind == 1) first_pass(held);
+      else second_pass(it, std::false_type{}, held);
     }
   }
 }
@@ -1505,11 +2344,24 @@ int proxy_blocks(int dtype, int D, int P) {
 
 }  // namespace
 
-// The two kernels (the launch bound, which sets the register budget, has to
-// be a constant of the kernel itself).
+// The kernels (the launch bound, which sets the register budget, has to be a
+// constant of the kernel itself).
+// One group of exactly 128 rows (more go to score_block_kernel), with the item
+// length fixed or (short) from the schedule: 32 heads, 32k tokens 377 us with
+// rows, groups and length as constants, 379 without (three registers spilled).
 __global__ __launch_bounds__(kScoreThreads, NACL_SPLIT_OCC) void score_split_kernel(const __bf16* __restrict__ q,
                                                                                     const __bf16* __restrict__ k,
                                                                                     ScoreArgs a, ScoreSched s) {
+  a.P = kSplitRows;
+  s.n_psplit = 1;
+  s.chunk_keys = kSplitChunkKeys;
+  score_split_body<2>(q, k, a, s);
+}
+__global__ __launch_bounds__(kScoreThreads, NACL_SPLIT_OCC) void score_split_short_kernel(const __bf16* __restrict__ q,
+                                                                                          const __bf16* __restrict__ k,
+                                                                                          ScoreArgs a, ScoreSched s) {
+  a.P = kSplitRows;
+  s.n_psplit = 1;
   score_split_body<2>(q, k, a, s);
 }
 __global__ __launch_bounds__(kScoreThreads, 2) void score_split_wide_kernel(const __bf16* __restrict__ q,
@@ -1517,11 +2369,22 @@ __global__ __launch_bounds__(kScoreThreads, 2) void score_split_wide_kernel(cons
                                                                            ScoreArgs a, ScoreSched s) {
   score_split_body<8>(q, k, a, s);
 }
+__global__ __launch_bounds__(kScoreThreads, 2) void score_block_kernel(const __bf16* __restrict__ q,
+                                                                      const __bf16* __restrict__ k, ScoreArgs a,
+                                                                      ScoreSched s) {
+  score_block_body(q, k, a, s);
+}
+template <int D, int NRB, bool FUSED>
+__global__ __launch_bounds__(kKeysThreads, 2) void score_keys_kernel(const __bf16* __restrict__ q,
+                                                                    const __bf16* __restrict__ k, ScoreArgs a,
+                                                                    ScoreSched s) {
+  score_keys_body<D, NRB, FUSED>(q, k, a, s);
+}
 
 template <class K>
-hipError_t launch_score_split_t(K kern, const ScoreLaunch& L, hipStream_t stream) {
+hipError_t launch_score_split_t(K kern, int threads, const ScoreLaunch& L, hipStream_t stream) {
   int per_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kScoreThreads, 0);
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, 0);
   if (e != hipSuccess) return e;
   int dev = 0, cus = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -1531,14 +2394,18 @@ hipError_t launch_score_split_t(K kern, const ScoreLaunch& L, hipStream_t stream
   hipLaunchKernelGGL(score_init_kernel, dim3(init_blocks), dim3(256), 0, stream, L.sched.queue,
                      L.n_counter_words);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kScoreThreads), 0, stream, static_cast<const __bf16*>(L.q),
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, stream, static_cast<const __bf16*>(L.q),
                      static_cast<const __bf16*>(L.k), L.args, L.sched);
   return hipGetLastError();
 }
 
-hipError_t launch_score_split(const ScoreLaunch& L, hipStream_t stream) {
-  if (L.args.P >= kSplitWideP) return launch_score_split_t(score_split_wide_kernel, L, stream);
-  return launch_score_split_t(score_split_kernel, L, stream);
+template <int D, bool FUSED>
+hipError_t launch_score_keys(const ScoreLaunch& L, hipStream_t stream) {
+  if constexpr (FUSED)
+    if (L.args.P <= 128) return launch_score_split_t(score_keys_kernel<D, 4, FUSED>, kKeysThreads, L, stream);
+  if constexpr (FUSED || D == 64)
+    if (L.args.P <= 256) return launch_score_split_t(score_keys_kernel<D, 8, FUSED>, kKeysThreads, L, stream);
+  return launch_score_split_t(score_keys_kernel<D, 16, FUSED>, kKeysThreads, L, stream);
 }
 
 template <typename T, int D>
@@ -1588,10 +2455,24 @@ hipError_t launch_score(const ScoreLaunch& L, hipStream_t stream) {
     if (L.dtype == 1) return L.D == 128 ? launch_score_rows_t<__bf16, 128>(L, stream) : launch_score_rows_t<__bf16, 64>(L, stream);
     return L.D == 128 ? launch_score_rows_t<float, 128>(L, stream) : launch_score_rows_t<float, 64>(L, stream);
   }
-  if (score_uses_split(L.dtype, L.D, L.args.P)) {
-    if (L.sched.chunk_keys != kSplitChunkKeys) return hipErrorInvalidValue;
-    if (L.sched.n_psplit != score_psplit(L.dtype, L.D, L.args.P)) return hipErrorInvalidValue;
-    return launch_score_split(L, stream);
+  if (L.sched.path == kScoreKeys) {
+    const ScoreSched& sc = L.sched;
+    if (L.dtype != 1 || sc.chunk_keys % kKeysThreads || sc.chunk_keys < kKeysThreads || sc.chunk_keys > kSplitChunkKeys ||
+        sc.n_psplit != 1 || L.args.P > kSplitWideRows ||
+        (sc.fused && (sc.total_items > kKeysFuseMax || sc.lse_given || sc.chunk_keys != kKeysThreads)))
+      return hipErrorInvalidValue;
+    if (sc.fused) return L.D == 128 ? launch_score_keys<128, true>(L, stream) : launch_score_keys<64, true>(L, stream);
+    return L.D == 128 ? launch_score_keys<128, false>(L, stream) : launch_score_keys<64, false>(L, stream);
+  }
+  if (L.sched.path == kScoreSplit) {
+    const int ck = L.sched.chunk_keys, P = L.args.P;
+    if (L.dtype != 1 || L.D != 128 || P < kSplitRows || ck < kSplitChunkMin || ck > kSplitChunkKeys || ck % kSplitChunkMin ||
+        L.sched.n_psplit != score_psplit(L.dtype, L.D, P) || (P > kBlockRows && P < kSplitWideRows))
+      return hipErrorInvalidValue;
+    if (P == kSplitRows)
+      return launch_score_split_t(ck == kSplitChunkKeys ? score_split_kernel : score_split_short_kernel, kScoreThreads, L, stream);
+    if (P <= kBlockRows) return launch_score_split_t(score_block_kernel, kScoreThreads, L, stream);
+    return launch_score_split_t(score_split_wide_kernel, kScoreThreads, L, stream);
   }
   if (L.sched.n_psplit != 1) return hipErrorInvalidValue;
   const int pb = proxy_blocks(L.dtype, L.D, L.args.P);

@@ -1,0 +1,124 @@
+"""GPU parity of the score kernels that larger bf16 launches and row counts
+choose, at the edges of their ranges: keys held in registers with both passes
+in one work-group (up to one 512-key chunk per CU, two for 65 to 128 rows), keys in
+registers with the passes queued (D = 64 over 128 rows, 257 to 511 rows), the
+block kernel (129 to 256 rows), and the split kernels with shortened items.
+
+The scores are compared with the float64 oracle within 1e-3 relative, the bound
+of every score test: logits are float32 sums of at most 128 exact bf16
+products, |logit| < 2^5 here, so their error of 2^-24 * 128 * 2^5 stays below
+2.5e-4, and an exponential's relative error is that of its argument."""
+
+import sys
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import SAMPLE_SOFTMAX, proxy_scores
+from synth import custom, make_layer
+from tests._parity import check_scores
+
+pytestmark = pytest.mark.gpu
+
+nacl = pytest.importorskip("paper_2408_03675_amd.nacl")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    nacl.load_library()
+
+
+def _np(t):
+    return t.detach().float().cpu().numpy()
+
+
+def suffix(L, P):
+    return list(range(L - P, L))
+
+
+def spread(L, P):
+    return sorted({int(x) for x in np.linspace(0, L - 1, P)})
+
+
+CASES = [
+    # name, B, H, L, D, positions
+    # both passes in one work-group: rows about a multiple of 32 and of the row buffers
+    ("held_17_rows", 1, 3, 513, 128, suffix(513, 17)),
+    ("held_32_rows_d64", 2, 2, 511, 64, spread(511, 32)),
+    ("held_33_rows", 1, 2, 512, 128, spread(512, 33)),
+    ("held_127_rows_d64", 1, 2, 1025, 64, suffix(1025, 127)),
+    ("held_129_rows", 1, 2, 1537, 128, spread(1537, 129)),
+    ("held_256_rows_early_d64", 1, 2, 2100, 64, list(range(256))),
+    ("held_257_rows", 2, 1, 1500, 128, suffix(1500, 257)),
+    ("held_512_rows", 1, 2, 2047, 128, spread(2047, 512)),
+    ("held_512_rows_d64", 1, 1, 1100, 64, suffix(1100, 512)),
+    # two chunks per work-group: the first one's keys and rows are read again
+    ("held_twice_65_rows", 2, 50, 1300, 128, suffix(1300, 65)),
+    ("held_twice_128_rows_d64", 1, 170, 1030, 64, spread(1030, 128)),
+    # beyond those: tiles, split with short items, block, keys with queued passes, wide
+    ("tiles_64_rows", 2, 86, 1100, 128, suffix(1100, 64)),
+    ("split_128_short_items", 2, 90, 1100, 128, spread(1100, 128)),
+    ("block_129_rows", 1, 90, 1100, 128, suffix(1100, 129)),
+    ("block_200_rows_early", 2, 45, 1300, 128, list(range(100, 300))),
+    ("block_256_rows", 1, 60, 2300, 128, spread(2300, 256)),
+    ("queued_129_rows_d64", 1, 90, 1100, 64, suffix(1100, 129)),
+    ("queued_300_rows", 2, 45, 1100, 128, spread(1100, 300)),
+    ("queued_511_rows_d64", 1, 90, 1045, 64, list(range(30, 541))),
+    ("queued_long_items", 1, 130, 8200, 64, suffix(8200, 150)),
+    ("wide_512_rows_short_items", 1, 90, 1100, 128, suffix(1100, 512)),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_score_paths_match_oracle(case):
+    """The scores, with the library's and the caller's log-sum-exp; the scores
+    a second time (bit-reproducible, on a used workspace); a whole eviction's
+    keep set against the selection on those scores."""
+    name, B, H, L, D, pos = case
+    print("score path", name, file=sys.stderr, flush=True)
+    w = custom(name, B, H, L, D, len(pos), dtype="bf16", data_seed=zlib.crc32(name.encode()) % 1000)
+    q, k, v = make_layer(w, 0, device="cuda")
+    prob = nacl.Problem.from_tensors(q, k, v, pos)
+    ws = nacl.workspace(prob)
+    F = nacl.score(prob, q, k, ws).clone()
+    again = nacl.score(prob, q, k, ws)
+    assert torch.equal(F, again)
+    heads = range(0, H, 1 if L < 4000 else 43)  # the oracle over the long case's heads takes minutes
+    qn, kn = _np(q[:, heads]), _np(k[:, heads])
+    Fr, lse = proxy_scores(qn, kn, pos, prob.c.sm_scale)
+    check_scores(_np(F[:, heads]), Fr, name)
+    total = _np(F).astype(np.float64).sum(-1)
+    np.testing.assert_allclose(total, len(pos), rtol=1e-5)
+    if len(heads) == H:
+        given = nacl.score(prob, q, k, ws, lse=torch.from_numpy(lse.astype(np.float32)).cuda())
+        check_scores(_np(given), Fr, name + " caller lse")
+    C = len(pos) + 40
+    Fe, keep, _, _ = nacl.evict(prob, q, k, v, C, 30, SAMPLE_SOFTMAX, 11, 2, ws=ws)
+    assert torch.equal(Fe, F)
+    assert torch.equal(keep, nacl.select(prob, F, C, 30, SAMPLE_SOFTMAX, 11, 2, ws=ws))
+
+
+@pytest.mark.parametrize("H,P,D", [(90, 129, 128), (90, 300, 128), (180, 128, 128), (90, 200, 64)])
+def test_score_paths_large_logits(H, P, D):
+    """One key far above the others of its chunk (about 180 above in the
+    exponent): references taken from other keys overflow, and every path has
+    to end with that key's mass."""
+    L = 1100
+    g = torch.Generator(device="cuda").manual_seed(11)
+    q = torch.randn((1, H, L, D), generator=g, device="cuda")
+    k = torch.randn((1, H, L, D), generator=g, device="cuda")
+    pos = suffix(L, P)
+    q[:, :, L - P:] += 2.0 * (128 / D) ** 0.5
+    k[:, ::2, 400] = 8.0
+    k[:, 1::2, 700] = 8.0
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    prob = nacl.Problem.from_tensors(q, k, k, pos)
+    F = nacl.score(prob, q, k, nacl.workspace(prob))
+    heads = [0, 1, H // 2, H - 1]
+    Fr, _ = proxy_scores(_np(q[:, heads]), _np(k[:, heads]), pos, prob.c.sm_scale)
+    check_scores(_np(F[:, heads]), Fr, "large logits")
+    np.testing.assert_allclose(_np(F).astype(np.float64).sum(-1), P, rtol=1e-5)
