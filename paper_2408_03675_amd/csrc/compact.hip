@@ -56,49 +56,52 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(CompactLaunch 
 // In place: row c of each head takes row keep[c] of the same head, in the
 // input's own layout.  keep is strictly ascending, so keep[c] >= c and the
 // rows a chunk of destinations [c0, c1) reads lie at or after c0: rows that
-// no earlier chunk writes.  One work-group per (head, K or V) walks the
-// chunks in order; inside a chunk every source is read (the barrier waits
-// for the loads) before any destination is written, since a source of one
-// row may be the destination of another row of the same chunk.  Rows with
+// no earlier chunk writes.  One work-group per (head, K or V, column slice)
+// walks the chunks in order; inside a chunk every source is read (the barrier
+// waits for the loads) before any destination is written, since a source of
+// one row may be the destination of another row of the same chunk.  Rows with
 // keep[c] == c stay where they are.
-constexpr int kInplaceThreads = 1024;
+//
+// A row's vectors keep their columns, so the order holds within each column
+// by itself, and slices of SLICE vectors need no word between their
+// work-groups: few heads still give enough loads in flight.  What bounds it is
+// memory latency (a chunk's indices, its rows, then the stores) until every CU
+// has work, and then HBM; a chunk's indices are read together, as a row's load
+// behind its own index only would wait for them one by one.  Whole rows and
+// indices one by one before, now: 4 heads of 131072 rows keeping 40000 (bf16,
+// 128) 368 -> 89 us; 32 heads, 32768 keeping 10000, 148 -> 67 (4.9 TB/s); 12
+// fp32 heads, 20001 keeping 7001, 135 -> 33; 128 heads, 16384 keeping 5000 (bf16,
+// 64) 63.6 -> 59.2; 128 heads, 6617 keeping 6553, 184 -> 182.
 constexpr int kInplaceVecs = 16;  // vectors per thread and chunk (all loads in flight at once)
 
-template <int VPR>
-__global__ __launch_bounds__(kInplaceThreads) void compact_inplace_kernel(CompactLaunch a) {
+template <int VPR, int SLICE, int THREADS>
+__global__ __launch_bounds__(THREADS) void compact_inplace_kernel(CompactLaunch a) {
+  static_assert(VPR % SLICE == 0 && THREADS % SLICE == 0);
   const int bh = blockIdx.x, b = bh / a.H, h = bh % a.H;
-  const bool is_v = blockIdx.y != 0;
+  const bool is_v = blockIdx.y % 2 != 0;
+  const int col = (int)(blockIdx.y / 2) * SLICE;
   const int64_t* st = is_v ? a.vs : a.ks;
-  u32x4* base = static_cast<u32x4*>(is_v ? a.v_out : a.k_out) + b * st[0] + h * st[1];
-  constexpr int vpr = VPR;
-  const int rows_per_chunk = kInplaceThreads * kInplaceVecs / vpr;
+  u32x4* base = static_cast<u32x4*>(is_v ? a.v_out : a.k_out) + b * st[0] + h * st[1] + col + threadIdx.x % SLICE;
+  constexpr int kRows = THREADS / SLICE;  // rows per vector of a thread
   const int32_t* keep = a.keep + (int64_t)bh * a.C;
-  for (int c0 = 0; c0 < a.C; c0 += rows_per_chunk) {
+  for (int c0 = 0; c0 < a.C; c0 += kRows * kInplaceVecs) {
     u32x4 x[kInplaceVecs];
-    int dst[kInplaceVecs];
+    int dst[kInplaceVecs], src[kInplaceVecs];
+#pragma unroll
+    for (int u = 0; u < kInplaceVecs; ++u) src[u] = keep[min(c0 + u * kRows + (int)threadIdx.x / SLICE, a.C - 1)];
 #pragma unroll
     for (int u = 0; u < kInplaceVecs; ++u) {
-      const int idx = u * kInplaceThreads + (int)threadIdx.x;
-      const int r = c0 + idx / vpr, vec = idx % vpr;
-      dst[u] = -1;
+      const int r = c0 + u * kRows + (int)threadIdx.x / SLICE, j = src[u];
+      const bool ok = (unsigned)j < (unsigned)a.L;
+      dst[u] = r < a.C && j != r ? r : -1;
       x[u] = u32x4{0u, 0u, 0u, 0u};
-      if (r < a.C) {
-        const int j = keep[r];
-        if ((unsigned)j >= (unsigned)a.L) {
-          dst[u] = r;  // zero row
-          if (vec == 0) flag_bad_index(a.health);
-        } else if (j != r) {
-          x[u] = base[(int64_t)j * st[2] + vec];
-          dst[u] = r;
-        }
-      }
+      if (dst[u] >= 0 && ok) x[u] = base[(int64_t)j * st[2]];
+      if (dst[u] >= 0 && !ok && col == 0 && threadIdx.x % SLICE == 0) flag_bad_index(a.health);
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kInplaceVecs; ++u) {
-      const int idx = u * kInplaceThreads + (int)threadIdx.x;
-      if (dst[u] >= 0) base[(int64_t)dst[u] * st[2] + idx % vpr] = x[u];
-    }
+    for (int u = 0; u < kInplaceVecs; ++u)
+      if (dst[u] >= 0) base[(int64_t)dst[u] * st[2]] = x[u];
   }
 }
 
@@ -195,7 +198,16 @@ namespace {
 template <int VPR>
 hipError_t launch_compact_t(const CompactLaunch& a, hipStream_t stream) {
   if (a.in_place) {
-    hipLaunchKernelGGL(compact_inplace_kernel<VPR>, dim3(a.B * a.H, 2), dim3(kInplaceThreads), 0, stream, a);
+    // Slices of 64 bytes while these give at most one work-group per CU (256);
+    // beyond, a line shared by two work-groups costs more than the parallelism
+    // gives, and slices are whole 128-byte lines.  64 against 128 bytes: 32
+    // heads of 16 vectors a row (256 work-groups) 66.6 against 80.9 us, 128
+    // heads 306 against 187.
+    const int BH = a.B * a.H;
+    if ((int64_t)2 * BH * (VPR / 4) <= 256)
+      hipLaunchKernelGGL((compact_inplace_kernel<VPR, 4, 512>), dim3(BH, 2 * (VPR / 4)), dim3(512), 0, stream, a);
+    else
+      hipLaunchKernelGGL((compact_inplace_kernel<VPR, 8, 1024>), dim3(BH, 2 * (VPR / 8)), dim3(1024), 0, stream, a);
     return hipGetLastError();
   }
   constexpr int rows_per_block = kCompactThreads / VPR;
