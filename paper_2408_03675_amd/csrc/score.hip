@@ -2432,7 +2432,12 @@ int score_rows_chunk(int dtype, int D, int L, int BH, int cus) {
     e = D == 128 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, score_rows_logits_kernel<float, 128>, kScoreThreads, 0)
                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, score_rows_logits_kernel<float, 64>, kScoreThreads, 0);
   if (e != hipSuccess || per_cu < 1) per_cu = 1;
-  const int64_t slots = (int64_t)per_cu * std::max(1, cus);
+  // Rounds of two work-groups per CU, also where three fit: longer chunks leave
+  // the column kernel fewer partials to merge.  A round of 128 heads of 6617
+  // rows (bf16, 128) 78.7 us, planned for three 81.0; 64 heads of 2100 (64)
+  // 40.0 and 42.0; 128 heads of 1100 (64) 41.1 and 42.9; 64 of 3016 (128) 45.6
+  // and 47.5.
+  const int64_t slots = (int64_t)std::min(per_cu, 2) * std::max(1, cus);
   // Fewest chunks per head (longest chunks), the rounds of resident
   // work-groups they take, then as many chunks as fill those rounds.
   const int64_t n_min = (L + kRowsChunkMax - 1) / kRowsChunkMax;
