@@ -170,14 +170,13 @@ def test_attention_rejects_unsupported():
         nacl.attention(prob, qb, qb, qb, lse_proxy=True)  # no proxy_pos_dev
 
 
-# Edges of the work-group forms: 128 or 256 rows per work-group (the second
-# from 64 work-groups of 256 rows on), waves of 64 rows, tiles of 64 keys,
-# heads that 8 XCDs do not divide, and groups of heads sharing K and V.
+# Edges of the work-groups of 128 rows, tiles of 64 keys, heads that 8 XCDs do
+# not divide, and groups of heads sharing K and V.
 TILE_CASES = [
     # B, H, q_group, L, D
-    (1, 1, 1, 63, 128), (1, 1, 1, 65, 64), (1, 3, 1, 127, 128), (2, 5, 1, 193, 64),   # 128-row work-groups
+    (1, 1, 1, 63, 128), (1, 1, 1, 65, 64), (1, 3, 1, 127, 128), (2, 5, 1, 193, 64),
     (1, 9, 1, 320, 128), (1, 4, 2, 255, 64),
-    (1, 67, 1, 65, 128), (2, 9, 4, 192, 64), (1, 64, 1, 256, 128), (4, 17, 1, 129, 64),  # 256-row work-groups
+    (1, 67, 1, 65, 128), (2, 9, 4, 192, 64), (1, 64, 1, 256, 128), (4, 17, 1, 129, 64),
     (1, 33, 1, 321, 128), (1, 9, 8, 257, 64), (1, 16, 1, 1025, 128),
 ]
 
@@ -217,3 +216,77 @@ def test_attention_rising_logits(D, H):
     assert np.isfinite(_f64(out)).all()
     assert np.abs(_f64(out) - Or).max() <= O_TOL * np.abs(_f64(v)).max()
     assert (np.abs(_f64(lse) - lr) <= LSE_ATOL + 2.0 ** -22 * np.abs(lr)).all()
+
+
+# Long rows of 128 with at least 256 work-groups of 256 rows: waves of 64 rows.
+# Whole tiles, one row in the last wave, waves without rows, grouped heads.
+LONG_CASES = [
+    # B, H, q_group, L, [B, L, H, D] layout
+    (1, 11, 1, 6144, False), (2, 3, 2, 6145, True), (1, 11, 1, 6335, False), (1, 2, 8, 6207, True),
+]
+
+
+@pytest.mark.parametrize("B,H,g,L,blhd", LONG_CASES)
+def test_attention_long_rows(B, H, g, L, blhd):
+    """64 consecutive rows (each of a wave's rows is rescaled by its own
+    factors), the first, middle and last rows."""
+    print("attention long", B, H, g, L, file=sys.stderr, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L + H)
+    shape = [(B, L, H * g, 128), (B, L, H, 128), (B, L, H, 128)] if blhd else [(B, H * g, L, 128), (B, H, L, 128), (B, H, L, 128)]
+    q, k, v = (torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16) for s in shape)
+    if blhd:
+        q, k, v = (x.transpose(1, 2) for x in (q, k, v))
+    prob = nacl.Problem.from_tensors(q, k, v, [L - 1])
+    out, lse, _ = nacl.attention(prob, q, k, v)
+    torch.cuda.synchronize()
+    assert torch.isfinite(lse).all()
+    again, lse2, _ = nacl.attention(prob, q, k, v)
+    assert torch.equal(out, again) and torch.equal(lse, lse2)
+    rows = np.unique(np.concatenate([np.arange(0, 300, 37), np.arange(2944, 3008), [L - 66, L - 65, L - 64, L - 2, L - 1]]))
+    heads = sorted({0, H // 2, H - 1})
+    for h in heads:
+        qs = slice(h * g, h * g + g)
+        _check(out[:, qs], lse[:, qs], q[:, qs], k[:, h:h + 1], v[:, h:h + 1], prob.c.sm_scale, g, f"long h{h}", rows=rows)
+
+
+@pytest.mark.parametrize("H,L,D", [(2, 700, 64), (2, 700, 128), (11, 6144, 128)])
+def test_attention_largest_probability_is_exact(H, L, D):
+    """A key whose logit lies less than 2^8 above the first tile's carries all of
+    the output (the other value rows are zeros).  Against the row's own maximum
+    its probability is 1, exact in bf16, so the output is w V with one rounding
+    to bf16: within 2^-8 of its size, and 2^-14 for the fp32 logit and sum.  A
+    probability of up to 2^8 would be rounded as well, by up to 2^-8 more."""
+    at = 70
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(D + H)
+    q = torch.zeros((1, H, L, D), device="cuda")
+    k, v = torch.zeros_like(q), torch.zeros_like(q)
+    q[..., 0] = 1.0 + 4.5 * torch.rand((1, H, L), generator=gen, device="cuda")  # logits of 1.4 .. 7.9 in base 2
+    k[:, :, at, 0] = 1.0
+    v[:, :, at] = torch.randn((1, H, D), generator=gen, device="cuda") + 2.0
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    prob = nacl.Problem.from_tensors(q, k, v, [L - 1], sm_scale=1.0)
+    out, lse, _ = nacl.attention(prob, q, k, v)
+    rows = torch.arange(at, L, device="cuda", dtype=torch.float64)
+    e = q[0, :, at:, 0].double().exp()
+    l = e + rows  # row r sees r other keys, whose logits are 0
+    ref = (e / l)[..., None] * v[0, :, at].double()[:, None]
+    err = ((out[0, :, at:].double() - ref).abs() / ref.abs().clamp_min(1e-30)).max().item()
+    assert err <= 2.0 ** -8 + 2.0 ** -14, err / 2.0 ** -8
+    assert (lse[0, :, at:].double() - l.log()).abs().max().item() <= LSE_ATOL
+
+
+@pytest.mark.parametrize("H,L", [(2, 700), (11, 6144)])
+def test_attention_nan_key_stays_in_its_rows(H, L):
+    """A key of NaNs makes the rows that see it NaN and no others."""
+    at = 333
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H)
+    q, k, v = (torch.randn((1, H, L, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    k[:, 1, at] = float("nan")
+    prob = nacl.Problem.from_tensors(q, k, v, [L - 1])
+    out, lse, _ = nacl.attention(prob, q, k, v)
+    assert torch.isfinite(out[:, 0]).all() and torch.isfinite(out[:, 2:]).all()
+    assert torch.isfinite(out[:, 1, :at]).all() and torch.isfinite(lse[:, 1, :at]).all()
+    assert torch.isnan(out[:, 1, at:]).all() and torch.isnan(lse[:, 1, at:]).all()
