@@ -421,13 +421,20 @@ __device__ __forceinline__ void static_for(F&& f) {
 // at byte lds of the work-group's allocation.  An asm block, so that the
 // compiler does not make LDS reads of the tile in hand wait for the loads of
 // the next one; the kernel waits for them itself (dma_barrier).
+// (A vector instruction that writes a scalar register, as a spilled one's
+// reload does, has to be five wait states ahead of a load that reads it: two
+// instructions and three waits.  M0 is one of the compiler's own registers; it
+// is told of the write all the same.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t voff, uint32_t off, uint32_t lds) {
   uint32_t t;
-  asm volatile("s_mov_b32 m0, %1\n\tv_add_u32 %0, %2, %3\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds"
+  asm volatile("s_mov_b32 m0, %1\n\tv_add_u32 %0, %2, %3\n\ts_nop 2\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds"
                : "=&v"(t)
                : "s"(lds), "s"(off), "v"(voff), "s"(rsrc)
-               : "memory");
+               : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Every DMA of this wave and every LDS read it issued has completed, then
 // the work-group's barrier.
 __device__ __forceinline__ void dma_barrier() {
@@ -882,6 +889,7 @@ __global__ __launch_bounds__(64 * kLongWaves, 1) void attn_long_kernel(AttnLaunc
   }
   settle<true>(acc);
   for (int j = n_w; j < n_kv; ++j) middle(j);  // the other waves' tiles
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads past the last tile, which write zeros
 
   // Normalise and store: lane (hl, m32) holds O[8 (i / 4) + 4 hl + i % 4][32 dt
   // + m32].  Lanes 2 n and 2 n + 1 trade halves of two rows, so that each

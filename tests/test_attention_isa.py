@@ -3,7 +3,10 @@ not know their wait states, so its own instructions must not touch an
 accumulation register within 18 wait states of one that writes it (it might copy
 one, were it to allocate them differently), and nothing may be spilled to
 memory (the kernel counts its own loads).  Checked on the assembly of the
-source as the build compiles it."""
+source as the build compiles it.  Likewise for its loads in asm: a vector
+instruction may have written a scalar register that such a load reads (the
+reload of a spilled one does) right before the block, and the load has to be
+five wait states behind it."""
 
 import os
 import re
@@ -59,6 +62,34 @@ def _violations(asm):
     return bad, blocks
 
 
+def _load_waits(asm):
+    """Wait states inside each asm block ahead of its buffer load."""
+    out, waits = [], None
+    for line in asm.splitlines():
+        if "ASMSTART" in line:
+            waits = 0
+        elif "ASMEND" in line:
+            waits = None
+        elif waits is not None:
+            t = line.split(";")[0].strip()
+            if t.startswith("buffer_load"):
+                out.append(waits)
+            m = re.match(r"s_nop (\d+)", t)
+            waits += int(m.group(1)) + 1 if m else bool(t)
+    return out
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    if not (shutil.which("hipcc") or os.path.exists("/opt/rocm/bin/hipcc")):
+        pytest.skip("no hipcc")
+    out = tmp_path_factory.mktemp("asm") / "attention.s"
+    cmd = [build._hipcc()] + build.HIP_FLAGS + build.SOURCE_FLAGS["attention.hip"] + [
+        "--cuda-device-only", "-S", "-x", "hip", os.path.join(build.CSRC, "attention.hip"), "-o", str(out)]
+    subprocess.run(cmd, check=True, capture_output=True)
+    return out.read_text()
+
+
 def test_check_finds_an_early_copy():
     mfma = ";;#ASMSTART\nv_mfma_f32_32x32x16_bf16 a[0:15], v[0:3], v[4:7], a[0:15]\n;;#ASMEND\n"
     assert _violations(mfma + "v_accvgpr_mov_b32 a40, a3\n")[0]
@@ -67,15 +98,13 @@ def test_check_finds_an_early_copy():
     assert not _violations(mfma + mfma)[0]
 
 
-def test_accumulators_are_left_alone(tmp_path):
-    if not (shutil.which("hipcc") or os.path.exists("/opt/rocm/bin/hipcc")):
-        pytest.skip("no hipcc")
-    out = tmp_path / "attention.s"
-    cmd = [build._hipcc()] + build.HIP_FLAGS + build.SOURCE_FLAGS["attention.hip"] + [
-        "--cuda-device-only", "-S", "-x", "hip", os.path.join(build.CSRC, "attention.hip"), "-o", str(out)]
-    subprocess.run(cmd, check=True, capture_output=True)
-    asm = out.read_text()
-    bad, blocks = _violations(asm)
+def test_accumulators_are_left_alone(assembly):
+    bad, blocks = _violations(assembly)
     assert blocks == 64  # two steps of 32 value products
     assert not bad, bad[:5]
-    assert "scratch_" not in asm
+    assert "scratch_" not in assembly
+
+
+def test_loads_wait_for_their_scalar_registers(assembly):
+    waits = _load_waits(assembly)
+    assert waits and min(waits) >= 5
