@@ -1953,6 +1953,12 @@ __device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, co
   __shared__ int item_s, last_s;
   __shared__ __attribute__((aligned(16))) int pos_g[kGroup];
   __shared__ __attribute__((aligned(16))) float lse_g[kGroup];
+  // Pass 2: the last positions of the item's rows whose log-sum-exp is -inf or
+  // NaN (their logits are NaN, or the caller says so; -1: none).  A key that a
+  // row does not see has a logit of -inf there, whose exponential is 0 only
+  // against a log-sum-exp that is finite or +inf: such rows take +inf, and the
+  // keys up to their positions get the infinity or NaN they stand for.
+  __shared__ int odd_p[2];
   // Pass 1: the waves' (reference, sum) of 256 rows, then the merge of a
   // head's partials; pass 2: the item's column sums.
   constexpr int kHalf = NRB < 8 ? NRB : 8;
@@ -2040,6 +2046,7 @@ __device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, co
       int64_t unused;
       pos_g[i] = i < gn ? row_position(a, i, unused) : -1;
     }
+    if (threadIdx.x < 2) odd_p[threadIdx.x] = -1;
     __syncthreads();
     constexpr int kBatch = 8;  // loads in flight per thread
     const int n = nrb * 32 * kChunksRow;
@@ -2198,8 +2205,12 @@ __device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, co
     if (!fresh) {
       const float* lse = s.lse_given ? s.lse_in : s.lse2;
       const float lse_mul = s.lse_given ? s.lse_mul : 1.0f;
-      for (int i = threadIdx.x; i < kGroup; i += kT)
-        lse_g[i] = i < gn ? load_coherent(lse + lse_index(a, s, bh, i)) * lse_mul : INFINITY;
+      for (int i = threadIdx.x; i < kGroup; i += kT) {
+        const float v = i < gn ? load_coherent(lse + lse_index(a, s, bh, i)) * lse_mul : INFINITY;
+        const bool odd = !(v > -INFINITY);
+        lse_g[i] = odd ? INFINITY : v;
+        if (odd) atomicMax(&odd_p[v == -INFINITY ? 0 : 1], pos_g[i]);
+      }
       __syncthreads();
       const __amdgpu_buffer_rsrc_t rsrc = keys_rsrc();
       const float* lse_l = lse_g + 4 * hl;  // rows 8 (i / 4) + i % 4 of the lane half
@@ -2264,7 +2275,11 @@ __device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, co
             });
         }
         auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(cs[0]), __float_as_uint(cs[1]), false, false);
-        col_lds[(j * kWv + wave) * 64 + lane] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+        float sum = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+        const int key = key0 + lane, o = opaque(0);
+        if (key <= odd_p[o]) sum += INFINITY;
+        if (key <= odd_p[o + 1]) sum = __builtin_nanf("");
+        col_lds[(j * kWv + wave) * 64 + lane] = sum;
       }
     }
     finish_columns<kT>(a, s, it, bh, chunk_key0, fresh, kGroup, col_lds, last_s, chunk_gumbel_keys);

@@ -122,3 +122,54 @@ def test_score_paths_large_logits(H, P, D):
     Fr, _ = proxy_scores(_np(q[:, heads]), _np(k[:, heads]), pos, prob.c.sm_scale)
     check_scores(_np(F[:, heads]), Fr, "large logits")
     np.testing.assert_allclose(_np(F).astype(np.float64).sum(-1), P, rtol=1e-5)
+
+
+ODD_CASES = [
+    # name, H, L, D, P, dtype: one case per kernel
+    ("held_200", 2, 1100, 128, 200, "bf16"), ("held_40_d64", 2, 1100, 64, 40, "bf16"), ("queued_300", 90, 1100, 128, 300, "bf16"),
+    ("queued_200_d64", 90, 1100, 64, 200, "bf16"), ("split_128", 180, 1100, 128, 128, "bf16"),
+    ("block_200", 90, 1100, 128, 200, "bf16"), ("wide_512", 90, 1100, 128, 512, "bf16"),
+    ("tiles_100", 180, 1100, 128, 100, "bf16"), ("tiles_f32", 3, 700, 64, 40, "f32"), ("few_rows", 3, 700, 128, 12, "bf16"),
+]
+
+
+@pytest.mark.parametrize("case", ODD_CASES, ids=[c[0] for c in ODD_CASES])
+def test_score_odd_row_stays_below_its_position(case):
+    """A query row of NaNs, and caller log-sum-exps of -inf, NaN and +inf: the
+    scores of keys past the row's position are those of the other rows."""
+    name, H, L, D, P, dt = case
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dtype = torch.bfloat16 if dt == "bf16" else torch.float32
+    q, k = (torch.randn((1, H, L, D), generator=g, device="cuda").to(dtype) for _ in range(2))
+    pos = spread(L - 90, P)
+    P = len(pos)
+    prob = nacl.Problem.from_tensors(q, k, k, pos)
+    ws = nacl.workspace(prob)
+    heads = [0, H - 1]
+    Fr, lse = proxy_scores(_np(q[:, heads]), _np(k[:, heads]), pos, prob.c.sm_scale)
+    qn, kn = _np(q[0, heads]).astype(np.float64), _np(k[0, heads]).astype(np.float64)
+
+    def others(r):
+        """The scores without row r."""
+        a = np.einsum("hd,hld->hl", qn[:, pos[r]], kn) * prob.c.sm_scale
+        return Fr[0] - np.where(np.arange(L)[None] <= pos[r], np.exp(a - lse[0, :, r, None]), 0.0)
+
+    r = P // 2
+    odd = q.clone()
+    odd[:, :, pos[r]] = float("nan")
+    F = _np(nacl.score(prob, odd, k, ws))[0, heads]
+    check_scores(F[:, pos[r] + 1:], others(r)[:, pos[r] + 1:], name + " NaN row")
+    assert np.isnan(F[:, :pos[r] + 1]).all()
+
+    full = torch.zeros((1, H, P), device="cuda")
+    full[:, heads] = torch.from_numpy(lse.astype(np.float32)).cuda()
+    for r, x in ((P // 3, -np.inf), (P // 2, np.nan), (2 * P // 3, np.inf)):
+        given = full.clone()
+        given[:, :, r] = float(x)
+        F = _np(nacl.score(prob, q, k, ws, lse=given))[0, heads]
+        want = others(r)
+        check_scores(F[:, pos[r] + 1:], want[:, pos[r] + 1:], f"{name} log-sum-exp {x}")
+        if x == np.inf:
+            assert (np.abs(F - want) <= 1e-3 * Fr[0]).all()  # the row adds nothing
+        else:
+            assert (np.isposinf if x == -np.inf else np.isnan)(F[:, :pos[r] + 1]).all()
