@@ -1081,52 +1081,49 @@ __device__ __forceinline__ void wait_lse(const ScoreSched& s, int bh) {
   __syncthreads();
 }
 
-// The end of a pass-2 item whose column sums are in col_lds (fresh: none were
-// written): with items split along the rows the chunk's last one adds all of
-// them; then the scores and, inside a whole eviction, their Gumbel keys.
-template <int kT, class Keys>
-__device__ __forceinline__ void finish_columns(const ScoreArgs& a, const ScoreSched& s, const ItemRef& it, int bh,
-                                               int chunk_key0, bool fresh, int group, float* col_lds, int& last_s,
-                                               Keys&& chunk_gumbel_keys) {
+// With items split along the rows: publishes the item's column sums (seen: some
+// row of its group sees the chunk), and the chunk's last item adds the groups'
+// sums in group order, as one item over every group would, into col_lds.
+// Returns whether this is that item.  Every thread calls it.
+template <int kT>
+__device__ __forceinline__ bool merge_groups(const ScoreArgs& a, const ScoreSched& s, const ItemRef& it, int bh,
+                                             int chunk_key0, bool seen, int group, float* col_lds, int& last_s) {
+  const int64_t cidx = (int64_t)bh * s.n_chunks + it.chunk;
+  float* cp = s.colpart + cidx * s.n_psplit * s.chunk_keys;
+  if (seen)
+    for (int q4 = 4 * (int)threadIdx.x; q4 < s.chunk_keys; q4 += 4 * kT)
+      store_coherent16(cp + it.psl * s.chunk_keys + q4,
+                       __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4*>(col_lds + q4)));
+  wait_stores();
   __syncthreads();
-  bool write = true;
-  if (s.n_psplit > 1) {
-    // Publish this group's column sums (none if no row of it sees the
-    // chunk); the chunk's last item adds the groups' sums in group order,
-    // as one item over every group would, and writes the scores.
-    const int64_t cidx = (int64_t)bh * s.n_chunks + it.chunk;
-    float* cp = s.colpart + cidx * s.n_psplit * s.chunk_keys;
-    if (!fresh)
-      for (int q4 = 4 * (int)threadIdx.x; q4 < s.chunk_keys; q4 += 4 * kT)
-        store_coherent16(cp + it.psl * s.chunk_keys + q4,
-                         __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4*>(col_lds + q4)));
-    wait_stores();
-    __syncthreads();
-    if (threadIdx.x == 0) last_s = atomicAdd(&s.chunk_cnt[cidx], 1u) == (unsigned)(s.n_psplit - 1);
-    __syncthreads();
-    write = last_s != 0;
-    if (write) {
-      for (int idx = threadIdx.x; idx < s.chunk_keys; idx += kT) {
-        float acc = 0.f;
-        for (int pg = 0; pg < s.n_psplit; ++pg) {
-          int64_t unused;
-          const int lr = min(a.P, (pg + 1) * group) - 1;  // the group's last row
-          if (row_position(a, lr, unused) >= chunk_key0) acc += load_coherent(cp + pg * s.chunk_keys + idx);
-        }
-        col_lds[idx] = acc;
-      }
-      __syncthreads();
+  if (threadIdx.x == 0) last_s = atomicAdd(&s.chunk_cnt[cidx], 1u) == (unsigned)(s.n_psplit - 1);
+  __syncthreads();
+  if (!last_s) return false;
+  for (int idx = threadIdx.x; idx < s.chunk_keys; idx += kT) {
+    float acc = 0.f;
+    for (int pg = 0; pg < s.n_psplit; ++pg) {
+      int64_t unused;
+      const int lr = min(a.P, (pg + 1) * group) - 1;  // the group's last row
+      if (row_position(a, lr, unused) >= chunk_key0) acc += load_coherent(cp + pg * s.chunk_keys + idx);
     }
+    col_lds[idx] = acc;
   }
-  if (write) {
-    float* F = s.scores + (int64_t)bh * a.L;
-    auto col_of = [&](int idx) -> float { return col_lds[idx]; };
-    for (int idx = threadIdx.x; idx < s.chunk_keys; idx += kT) {
-      const int key = chunk_key0 + idx;
-      if (key < a.L) F[key] = col_of(idx);
-    }
-    if (s.gkeys) chunk_gumbel_keys(col_of);
+  __syncthreads();
+  return true;
+}
+
+// The scores of a chunk whose column sums are in col_lds and, inside a whole
+// eviction, their Gumbel keys.
+template <int kT, class Keys>
+__device__ __forceinline__ void write_columns(const ScoreArgs& a, const ScoreSched& s, int bh, int chunk_key0,
+                                              const float* col_lds, Keys&& chunk_gumbel_keys) {
+  float* F = s.scores + (int64_t)bh * a.L;
+  auto col_of = [&](int idx) -> float { return col_lds[idx]; };
+  for (int idx = threadIdx.x; idx < s.chunk_keys; idx += kT) {
+    const int key = chunk_key0 + idx;
+    if (key < a.L) F[key] = col_of(idx);
   }
+  if (s.gkeys) chunk_gumbel_keys(col_of);
 }
 
 // WB proxy blocks of 16 per wave, so proxy groups of 64 * WB: WB = 2 (groups
@@ -1259,25 +1256,19 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
       }
     };
 
-    // The item's proxy rows [gb, ge): every row, or one group of them.
-    const int gb = s.n_psplit > 1 ? it.psl * kSplitGroup : 0;
-    const int ge = s.n_psplit > 1 ? min(a.P, gb + kSplitGroup) : a.P;
+    // The item's proxy rows [g0, g0 + gn): every row, or one group of them.
+    const int g0 = it.psl * kSplitGroup;
+    const int gn = min(kSplitGroup, a.P - g0);
     if (it.kind == 1) {
       // ---------------- pass 1: per-chunk (reference, sum) of every proxy row
       float2* part = s.partials + ((int64_t)bh * s.n_chunks + it.chunk) * a.P;
-      if (beyond)
-        for (int i = gb + threadIdx.x; i < ge; i += kScoreThreads)
-          store_coherent(part + i, make_float2(-INFINITY, 0.f));
-      for (int g0 = gb; g0 < (beyond ? gb : ge); g0 += kSplitGroup) {
-        const int gn = min(kSplitGroup, a.P - g0);
-        load_group(g0, gn);
-        if (pos_g[gn - 1] < chunk_key0) {
-          // No row of the group sees this chunk (rows are sorted by
-          // position): nothing to stream or compute.
-          for (int i = threadIdx.x; i < gn; i += kScoreThreads)
-            store_coherent(part + g0 + i, make_float2(-INFINITY, 0.f));
-          continue;
-        }
+      load_group(g0, gn);
+      if (pos_g[gn - 1] < chunk_key0) {
+        // No row sees this chunk (rows are sorted by position): nothing to
+        // stream or compute.
+        for (int i = threadIdx.x; i < gn; i += kScoreThreads)
+          store_coherent(part + g0 + i, make_float2(-INFINITY, 0.f));
+      } else {
         frag_t qf[WB][kS];
         int first, last;
         load_wave_q(gn, qf, first, last);
@@ -1402,11 +1393,9 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
       if (!s.lse_given) wait_lse(s, bh);
       const float* lse = s.lse_given ? s.lse_in : s.lse2;
       const float lse_mul = s.lse_given ? s.lse_mul : 1.0f;
-      bool fresh = true;  // the item's columns are not yet written
-      for (int g0 = gb; g0 < ge; g0 += kSplitGroup) {
-        const int gn = min(kSplitGroup, a.P - g0);
-        load_group(g0, gn);
-        if (pos_g[gn - 1] < chunk_key0) continue;  // no row of the group sees this chunk
+      load_group(g0, gn);
+      const bool seen = pos_g[gn - 1] >= chunk_key0;  // some row of the group sees this chunk
+      if (seen) {
         frag_t qf[WB][kS];
         int first, last;
         load_wave_q(gn, qf, first, last);
@@ -1460,8 +1449,7 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
         auto reduce_stage = [&](int t0) {  // tiles t0 .. t0 + 3
           if (wave == 0) {
             const float z = ((stage[0][lane] + stage[1][lane]) + stage[2][lane]) + stage[3][lane];
-            const int idx = t0 * 16 + lane;
-            col_lds[idx] = (fresh ? 0.f : col_lds[idx]) + z;
+            col_lds[t0 * 16 + lane] = z;
           }
         };
         k_tiles([&](int t, const frag_t (&kf)[kS], auto u_c) {
@@ -1485,9 +1473,16 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
         });
         __syncthreads();
         reduce_stage(n_tiles - 4);
-        fresh = false;
+      } else {
+        for (int i = threadIdx.x; i < s.chunk_keys; i += kScoreThreads) col_lds[i] = 0.f;
       }
-      finish_columns<kScoreThreads>(a, s, it, bh, chunk_key0, fresh, kSplitGroup, col_lds, last_s, chunk_gumbel_keys);
+      __syncthreads();
+      bool write = true;
+      if constexpr (WB == 8) {
+        if (s.n_psplit > 1)
+          write = merge_groups<kScoreThreads>(a, s, it, bh, chunk_key0, seen, kSplitGroup, col_lds, last_s);
+      }
+      if (write) write_columns<kScoreThreads>(a, s, bh, chunk_key0, col_lds, chunk_gumbel_keys);
     }
   }
 }
@@ -1921,7 +1916,8 @@ __device__ __forceinline__ void score_block_body(const __bf16* __restrict__ q, c
       put_stage(done);
       __syncthreads();
       reduce_stage(n_tiles - 2);
-      finish_columns<kScoreThreads>(a, s, it, bh, chunk_key0, false, kGroup, col_lds, last_s, chunk_gumbel_keys);
+      __syncthreads();
+      write_columns<kScoreThreads>(a, s, bh, chunk_key0, col_lds, chunk_gumbel_keys);
     }
   }
 }
@@ -2193,7 +2189,7 @@ __device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, co
         for (int e = 0; e < n; ++e) gk[j0 + e] = kv[e];
       }
     };
-    if (chunk_key0 > a.p_last) {  // no row sees the chunk
+    if (chunk_key0 > pos_g[gn - 1]) {  // no row sees the chunk
       float* F = s.scores + (int64_t)bh * a.L;
       const int end = min(chunk_key0 + s.chunk_keys, a.L);
       for (int j = chunk_key0 + threadIdx.x; j < end; j += kT) F[j] = 0.f;
@@ -2201,8 +2197,7 @@ __device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, co
       return;
     }
     if (!s.lse_given) wait_lse(s, bh);
-    const bool fresh = chunk_key0 > pos_g[gn - 1];  // no row of the group sees the chunk
-    if (!fresh) {
+    {
       const float* lse = s.lse_given ? s.lse_in : s.lse2;
       const float lse_mul = s.lse_given ? s.lse_mul : 1.0f;
       for (int i = threadIdx.x; i < kGroup; i += kT) {
@@ -2282,7 +2277,8 @@ __device__ __forceinline__ void score_keys_body(const __bf16* __restrict__ q, co
         col_lds[(j * kWv + wave) * 64 + lane] = sum;
       }
     }
-    finish_columns<kT>(a, s, it, bh, chunk_key0, fresh, kGroup, col_lds, last_s, chunk_gumbel_keys);
+    __syncthreads();
+    write_columns<kT>(a, s, bh, chunk_key0, col_lds, chunk_gumbel_keys);
   };
 
   auto take = [&]() {
