@@ -284,9 +284,15 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
       sc.path = nacl::kScoreKeys;
       sc.fused = 1;
       sc.chunk_keys = nacl::kKeysThreads;
-    } else if (p->D == 128 && rows >= nacl::kSplitRows && (rows <= nacl::kBlockRows || rows >= nacl::kSplitWideRows)) {
-      // Rows that fit one work-group's registers (128, 129 to 256) or wide
-      // lists (512 and more: the matrix cores bound it, see score.hip).
+    } else if (p->D == 128 && rows >= nacl::kSplitWideRows) {
+      // Long lists: the matrix cores bound it, see score.hip.
+      sc.path = nacl::kScoreSplit;
+    } else if (p->D == 128 && rows > nacl::kSplitMin && rows <= nacl::kBlockRows) {
+      // Rows that fit one work-group's registers.  Up to 64 rows the tile kernel
+      // holds them at twice the work-groups: 32 heads of 32k keys, 64 rows 115 us,
+      // split 153; 65 rows 160 and 157, 96 rows 169 and 158, with the caller's
+      // log-sum-exp 99 and 66; 80 heads of 4096 keys, 65 rows 71 and 74, 96 rows
+      // 76 and 74.
       sc.path = nacl::kScoreSplit;
     } else if (rows > nacl::kSplitRows && rows <= nacl::kSplitWideRows) {
       // D = 64, or 257 to 511 rows of D = 128.  32 heads of 32k keys, D = 64,
@@ -302,7 +308,7 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
       // rows, 16 heads of 32k keys: 256 items 123, 512 103; 24 heads: 384
       // items 141.5, 768 143.8.  400 rows, 12 heads of 32k keys: 384 items
       // 127, 768 151.
-      const int per_cu = sc.path == nacl::kScoreSplit && rows != nacl::kSplitRows ? 2 : 1;
+      const int per_cu = sc.path == nacl::kScoreSplit && rows > nacl::kSplitRows ? 2 : 1;
       sc.chunk_keys = nacl::kSplitChunkKeys;
       while (sc.n_psplit == 1 && sc.chunk_keys > nacl::kSplitChunkMin && items_of(sc.chunk_keys) < (int64_t)per_cu * cus)
         sc.chunk_keys /= 2;

@@ -36,22 +36,22 @@ constexpr int kScoreTpwMin = 8;
 constexpr int kScoreTpwMax = NACL_SCORE_TPW_MAX;
 constexpr int kScoreWavesPerSimd = NACL_SCORE_WAVES;
 constexpr int kScoreWaves = 4;  // waves per work-group, each owning a quarter of the item's keys
-// Proxy-split variants (bf16, D = 128, 128 to kBlockRows proxy rows or at
-// least kSplitWideRows): the waves of a block share one ring of K tiles and
-// split the rows, so an item is kSplitChunkKeys keys.
+// Proxy-split variants (bf16, D = 128, more than kSplitMin proxy rows up to
+// kBlockRows, and many more): the waves of a block share one ring of K tiles
+// and split the rows, so an item is up to kSplitChunkKeys keys.
 #ifndef NACL_SPLIT_CHUNK
 #define NACL_SPLIT_CHUNK 2048
 #endif
 constexpr int kSplitChunkKeys = NACL_SPLIT_CHUNK;
 constexpr int kSplitChunkMin = 512;  // shorter items where the heads are few or short
-constexpr int kSplitRows = 128;      // rows of the split kernel
-constexpr int kBlockRows = 256;      // most rows of the block kernel
-inline bool score_uses_split(int dtype, int D, int P) { return dtype == 1 && D == 128 && P >= kSplitRows; }
-// Proxy rows per group of the wide split kernel (from this many rows on it
-// is the one launched), and its items per chunk along the rows.
+constexpr int kSplitMin = 64;    // with at most this many rows: tiles
+constexpr int kSplitRows = 128;  // most rows of the split kernel
+constexpr int kBlockRows = 256;  // most rows of the block kernel
+// Proxy rows per group of the wide split kernel, and its items per chunk along
+// the rows.
 constexpr int kSplitWideRows = 512;
 inline int score_psplit(int dtype, int D, int P) {
-  return score_uses_split(dtype, D, P) && P > kSplitWideRows ? (P + kSplitWideRows - 1) / kSplitWideRows : 1;
+  return dtype == 1 && D == 128 ? std::max(1, (P + kSplitWideRows - 1) / kSplitWideRows) : 1;
 }
 // Few proxy rows (one query row per head in generation-phase eviction, the
 // single-token proxy set): the logits of every key are kept in the workspace

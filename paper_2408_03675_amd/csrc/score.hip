@@ -27,9 +27,9 @@
 // For bf16 inputs other layouts replace this one (below; the choice by rows
 // and items is run_score's): score_keys_kernel for small launches, whose work-
 // groups do both passes over keys they hold, and for 129 to 512 rows of D = 64
-// and 257 to 511 of D = 128; score_split_kernel (128 rows of D = 128) and
-// score_split_wide_kernel (512 and more), where the waves of a block share the
-// tile ring and split the proxy group; score_block_kernel (129 to 256 rows).
+// and many of D = 128; score_split_kernel (65 to 128 rows of D = 128) and
+// score_split_wide_kernel (long lists), where the waves of a block share the
+// tile ring and split the rows; score_block_kernel (129 to 256 rows).
 // The queue, the passes, the merge and reproducibility are the same.
 //
 // Work-groups take items from a queue counter in a fixed order: the pass-1
@@ -990,7 +990,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_rows_column_kernel(ScoreA
 }
 
 // ---------------------------------------------------------------------------
-// Proxy-split variant: bf16, D = 128, groups of 128 proxies.  The four waves
+// Proxy-split variant: bf16, D = 128, up to 128 proxies.  The four waves
 // of a block share one LDS ring of K tiles and split the proxy group: wave w
 // takes proxies [32w, 32w + 32) of every tile, so it holds a quarter of the
 // group's Q fragments and four blocks fit on a CU (more waves to hide the
@@ -1126,10 +1126,10 @@ __device__ __forceinline__ void write_columns(const ScoreArgs& a, const ScoreSch
   if (s.gkeys) chunk_gumbel_keys(col_of);
 }
 
-// WB proxy blocks of 16 per wave, so proxy groups of 64 * WB: WB = 2 (groups
-// of 128, four blocks per CU) or WB = 8 (groups of 512 for long proxy lists,
-// so that K is streamed once per pass instead of once per 128 proxies; two
-// blocks per CU).
+// WB proxy blocks of 16 per wave, so proxy groups of 64 * WB: WB = 2 (up to 128
+// rows, four blocks per CU) or WB = 8 (groups of 512 for long proxy lists, so
+// that K is streamed once per pass instead of once per 128 proxies; two blocks
+// per CU).  An item is one group of one chunk.
 template <int WB>
 __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                                                  const ScoreArgs& a, const ScoreSched& s) {
@@ -1402,7 +1402,7 @@ __device__ __forceinline__ void score_split_body(const __bf16* __restrict__ q, c
         for (int i = threadIdx.x; i < kSplitGroup; i += kScoreThreads)
           lse_g[i] = i < gn ? load_coherent(lse + lse_index(a, s, bh, g0 + i)) * lse_mul : INFINITY;
         __syncthreads();
-        // With groups of 128 proxies this lane's eight log-sum-exps (rows
+        // With up to 128 proxies this lane's eight log-sum-exps (rows
         // 4 g + e of its two proxy blocks) stay in registers for the whole
         // item; wider groups read them from LDS at every tile.
         constexpr int kLR = WB == 2 ? WB : 1;
@@ -2357,22 +2357,10 @@ int proxy_blocks(int dtype, int D, int P) {
 
 // The kernels (the launch bound, which sets the register budget, has to be a
 // constant of the kernel itself).
-// One group of exactly 128 rows (more go to score_block_kernel), with the item
-// length fixed or (short) from the schedule: 32 heads, 32k tokens 377 us with
-// rows, groups and length as constants, 379 without (three registers spilled).
 __global__ __launch_bounds__(kScoreThreads, NACL_SPLIT_OCC) void score_split_kernel(const __bf16* __restrict__ q,
                                                                                     const __bf16* __restrict__ k,
                                                                                     ScoreArgs a, ScoreSched s) {
-  a.P = kSplitRows;
-  s.n_psplit = 1;
-  s.chunk_keys = kSplitChunkKeys;
-  score_split_body<2>(q, k, a, s);
-}
-__global__ __launch_bounds__(kScoreThreads, NACL_SPLIT_OCC) void score_split_short_kernel(const __bf16* __restrict__ q,
-                                                                                          const __bf16* __restrict__ k,
-                                                                                          ScoreArgs a, ScoreSched s) {
-  a.P = kSplitRows;
-  s.n_psplit = 1;
+  s.n_psplit = 1;  // one group holds its rows
   score_split_body<2>(q, k, a, s);
 }
 __global__ __launch_bounds__(kScoreThreads, 2) void score_split_wide_kernel(const __bf16* __restrict__ q,
@@ -2482,11 +2470,10 @@ hipError_t launch_score(const ScoreLaunch& L, hipStream_t stream) {
   }
   if (L.sched.path == kScoreSplit) {
     const int ck = L.sched.chunk_keys, P = L.args.P;
-    if (L.dtype != 1 || L.D != 128 || P < kSplitRows || ck < kSplitChunkMin || ck > kSplitChunkKeys || ck % kSplitChunkMin ||
-        L.sched.n_psplit != score_psplit(L.dtype, L.D, P) || (P > kBlockRows && P < kSplitWideRows))
+    if (L.dtype != 1 || L.D != 128 || ck < kSplitChunkMin || ck > kSplitChunkKeys || ck % kSplitChunkMin ||
+        L.sched.n_psplit != score_psplit(L.dtype, L.D, P))
       return hipErrorInvalidValue;
-    if (P == kSplitRows)
-      return launch_score_split_t(ck == kSplitChunkKeys ? score_split_kernel : score_split_short_kernel, kScoreThreads, L, stream);
+    if (P <= kSplitRows) return launch_score_split_t(score_split_kernel, kScoreThreads, L, stream);
     if (P <= kBlockRows) return launch_score_split_t(score_block_kernel, kScoreThreads, L, stream);
     return launch_score_split_t(score_split_wide_kernel, kScoreThreads, L, stream);
   }

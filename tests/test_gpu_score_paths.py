@@ -2,7 +2,8 @@
 choose, at the edges of their ranges: keys held in registers with both passes
 in one work-group (up to one 512-key chunk per CU, two for 65 to 128 rows), keys in
 registers with the passes queued (D = 64 over 128 rows, 257 to 511 rows), the
-block kernel (129 to 256 rows), and the split kernels with shortened items.
+split kernel (65 to 128 rows), the block kernel (129 to 256 rows), and the split
+kernels with shortened items.
 
 The scores are compared with the float64 oracle within 1e-3 relative, the bound
 of every score test: logits are float32 sums of at most 128 exact bf16
@@ -62,6 +63,9 @@ CASES = [
     # beyond those: tiles, split with short items, block, keys with queued passes, wide
     ("tiles_64_rows", 2, 86, 1100, 128, suffix(1100, 64)),
     ("split_128_short_items", 2, 90, 1100, 128, spread(1100, 128)),
+    ("split_65_rows", 2, 130, 1100, 128, suffix(1100, 65)),
+    ("split_97_rows", 3, 61, 1500, 128, spread(1500, 97)),
+    ("split_127_rows_early", 2, 90, 1300, 128, list(range(300, 427))),
     ("block_129_rows", 1, 90, 1100, 128, suffix(1100, 129)),
     ("block_200_rows_early", 2, 45, 1300, 128, list(range(100, 300))),
     ("block_256_rows", 1, 60, 2300, 128, spread(2300, 256)),
@@ -102,7 +106,7 @@ def test_score_paths_match_oracle(case):
     assert torch.equal(keep, nacl.select(prob, F, C, 30, SAMPLE_SOFTMAX, 11, 2, ws=ws))
 
 
-@pytest.mark.parametrize("H,P,D", [(90, 129, 128), (90, 300, 128), (180, 128, 128), (90, 200, 64)])
+@pytest.mark.parametrize("H,P,D", [(90, 129, 128), (90, 300, 128), (180, 128, 128), (180, 70, 128), (90, 200, 64)])
 def test_score_paths_large_logits(H, P, D):
     """One key far above the others of its chunk (about 180 above in the
     exponent): references taken from other keys overflow, and every path has
@@ -129,7 +133,7 @@ ODD_CASES = [
     ("held_200", 2, 1100, 128, 200, "bf16"), ("held_40_d64", 2, 1100, 64, 40, "bf16"), ("queued_300", 90, 1100, 128, 300, "bf16"),
     ("queued_200_d64", 90, 1100, 64, 200, "bf16"), ("split_128", 180, 1100, 128, 128, "bf16"),
     ("block_200", 90, 1100, 128, 200, "bf16"), ("wide_512", 90, 1100, 128, 512, "bf16"),
-    ("tiles_100", 180, 1100, 128, 100, "bf16"), ("tiles_f32", 3, 700, 64, 40, "f32"), ("few_rows", 3, 700, 128, 12, "bf16"),
+    ("split_100", 180, 1100, 128, 100, "bf16"), ("tiles_50", 180, 1100, 128, 50, "bf16"), ("tiles_100_d64", 180, 1100, 64, 100, "bf16"), ("tiles_f32", 3, 700, 64, 40, "f32"), ("few_rows", 3, 700, 128, 12, "bf16"),
 ]
 
 
