@@ -279,12 +279,25 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
     // kernel holds up to 64 with twice the work-groups) nor do more (200 rows,
     // 400 chunks: 66.6, in the block kernel 62.4).
     const bool two = rows > nacl::kKeysTwoMin && rows <= nacl::kKeysTwoMax;
+    // 257 to 512 rows of D = 128: the wide kernel pads them to 512, so it takes
+    // them from the number on where that costs less than its pipeline gains, and
+    // where its items, two to a CU, fill the chip.  Keys in registers and wide, 32
+    // heads of 32k keys: 350 rows 279 and 293 us, 400 309 and 304, 511 351 and 309;
+    // 16 heads of them (256 items): 512 rows 177 and 179; 40 of 16k keys (320
+    // items): 400 rows 211 and 218, 480 232 and 222.  With the caller's
+    // log-sum-exp only a full group pays, and only heads of whole items: 32 heads
+    // of 128k keys, 480 rows 610 and 607, 512 605 and 585; 8 heads of them, 511
+    // rows 164 and 170; 600 heads of 1100 keys, 512 rows 151 and 172.
+    const int64_t items = items_of(nacl::kSplitChunkKeys);
+    const bool wide = rows <= nacl::kSplitWideRows && items > cus &&
+                      (sc.lse_given ? rows == nacl::kSplitWideRows && p->L >= nacl::kSplitChunkKeys
+                                    : rows > 384 && rows * items > (int64_t)nacl::kSplitWideRows * cus);
     const int64_t fuse_max = std::min<int64_t>((two ? 2 : 1) * (int64_t)cus, nacl::kKeysFuseMax);
     if (!sc.lse_given && rows <= nacl::kSplitWideRows && items_of(nacl::kKeysThreads) <= fuse_max) {
       sc.path = nacl::kScoreKeys;
       sc.fused = 1;
       sc.chunk_keys = nacl::kKeysThreads;
-    } else if (p->D == 128 && rows >= nacl::kSplitWideRows) {
+    } else if (p->D == 128 && (rows > nacl::kSplitWideRows || wide)) {
       // Long lists: the matrix cores bound it, see score.hip.
       sc.path = nacl::kScoreSplit;
     } else if (p->D == 128 && rows > nacl::kSplitMin && rows <= nacl::kBlockRows) {
@@ -295,9 +308,8 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
       // 76 and 74.
       sc.path = nacl::kScoreSplit;
     } else if (rows > nacl::kSplitRows && rows <= nacl::kSplitWideRows) {
-      // D = 64, or 257 to 511 rows of D = 128.  32 heads of 32k keys, D = 64,
-      // 200 rows 130 us, by tiles 267; 8 heads of 128k keys, D = 128, 400
-      // rows and the caller's log-sum-exp 534, in two groups 722.
+      // D = 64, or 257 to 512 rows of D = 128.  32 heads of 32k keys, D = 64,
+      // 200 rows 130 us, by tiles 267.
       sc.path = nacl::kScoreKeys;
     }
     if (sc.path != nacl::kScoreTiles && !sc.fused) {
@@ -305,9 +317,10 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
       // number fewer than one per CU (of the block and wide kernels, two of
       // which share a CU: two).  128 rows, 80 heads of 4096 keys: 160 items
       // 83 us, 320 66; 16 heads of 32k keys: 256 items 95, 512 106.  256
-      // rows, 16 heads of 32k keys: 256 items 123, 512 103; 24 heads: 384
-      // items 141.5, 768 143.8.  400 rows, 12 heads of 32k keys: 384 items
-      // 127, 768 151.
+      // rows, 16 heads of 32k keys: 256 items 134, 512 106; 24 heads: 384
+      // items 154, 768 141; 32: 512 items 177, 1024 184.  400 rows (keys in
+      // registers): 12 heads 192 items 147, 384 134; 16 heads 256 items 154,
+      // 512 177.
       const int per_cu = sc.path == nacl::kScoreSplit && rows > nacl::kSplitRows ? 2 : 1;
       sc.chunk_keys = nacl::kSplitChunkKeys;
       while (sc.n_psplit == 1 && sc.chunk_keys > nacl::kSplitChunkMin && items_of(sc.chunk_keys) < (int64_t)per_cu * cus)

@@ -1,7 +1,7 @@
 """GPU parity of the score kernels that larger bf16 launches and row counts
 choose, at the edges of their ranges: keys held in registers with both passes
 in one work-group (up to one 512-key chunk per CU, two for 65 to 128 rows), keys in
-registers with the passes queued (D = 64 over 128 rows, 257 to 511 rows), the
+registers with the passes queued (D = 64 over 128 rows, 257 to 512 rows), the
 split kernel (65 to 128 rows), the block kernel (129 to 256 rows), and the split
 kernels with shortened items.
 
@@ -73,7 +73,13 @@ CASES = [
     ("queued_300_rows", 2, 45, 1100, 128, spread(1100, 300)),
     ("queued_511_rows_d64", 1, 90, 1045, 64, list(range(30, 541))),
     ("queued_long_items", 1, 130, 8200, 64, suffix(8200, 150)),
-    ("wide_512_rows_short_items", 1, 90, 1100, 128, suffix(1100, 512)),
+    # 257 to 512 rows of D = 128 on both sides of the line between keys and wide:
+    # 385 and more rows past one item per CU, padded to 512 in the wide kernel
+    ("queued_384_rows", 4, 130, 700, 128, suffix(700, 384)),
+    ("wide_385_rows", 4, 130, 700, 128, spread(700, 385)),
+    ("wide_450_rows_early", 3, 130, 800, 128, list(range(100, 550))),
+    ("wide_512_rows", 2, 140, 1100, 128, suffix(1100, 512)),
+    ("queued_512_rows", 1, 90, 1100, 128, suffix(1100, 512)),
 ]
 
 
@@ -132,7 +138,7 @@ ODD_CASES = [
     # name, H, L, D, P, dtype: one case per kernel
     ("held_200", 2, 1100, 128, 200, "bf16"), ("held_40_d64", 2, 1100, 64, 40, "bf16"), ("queued_300", 90, 1100, 128, 300, "bf16"),
     ("queued_200_d64", 90, 1100, 64, 200, "bf16"), ("split_128", 180, 1100, 128, 128, "bf16"),
-    ("block_200", 90, 1100, 128, 200, "bf16"), ("wide_512", 90, 1100, 128, 512, "bf16"),
+    ("block_200", 90, 1100, 128, 200, "bf16"), ("wide_600", 90, 1100, 128, 600, "bf16"), ("wide_400", 520, 700, 128, 400, "bf16"),
     ("split_100", 180, 1100, 128, 100, "bf16"), ("tiles_50", 180, 1100, 128, 50, "bf16"), ("tiles_100_d64", 180, 1100, 64, 100, "bf16"), ("tiles_f32", 3, 700, 64, 40, "f32"), ("few_rows", 3, 700, 128, 12, "bf16"),
 ]
 
