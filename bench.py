@@ -147,8 +147,7 @@ def main():
 
     # Per-stage durations through the public entry points, timed with events
     # on the launch stream.  nacl_score = an init kernel (zeroes the work
-    # queue counters) + the score kernel (score_split_kernel for bf16,
-    # D = 128, 128 proxies and more than 512 chunks of 512 keys); nacl_select =
+    # queue counters) + the score kernel (nacl.score_kernel); nacl_select =
     # gumbel_keys_kernel + select_kernel_regs (select_kernel_global past 32k
     # tokens); nacl_compact = compact_kernel.  Inside nacl_evict the score
     # kernel also draws the Gumbel keys and the key kernel is skipped.
@@ -194,7 +193,6 @@ def main():
         raise RuntimeError(f"a kernel reported health bits {status:#x}; the timed results are invalid")
     ab = alg_bytes(w)
     fl = alg_flops(w)
-    split = w.dtype == "bf16" and w.D == 128 and w.P >= 128
     passes = 2  # logit passes the kernel executes
     peak_tf = F32_PEAK_TFLOPS if w.dtype == "f32" else BF16_PEAK_TFLOPS
     stages = {
@@ -218,14 +216,7 @@ def main():
     # Dominant kernel: the score kernel.  Its roofline is HBM (algorithmic
     # intensity P flop/byte, below the bf16 ridge of ~312): algorithmic bytes
     # = K read once + proxy rows of Q + F written, per launch (one layer).
-    chunks = w.B * w.H * -(-w.L // 512)
-    if w.dtype == "bf16" and 16 < w.P <= 512 and chunks <= (512 if 64 < w.P <= 128 else 256):
-        kname = "score_keys_kernel"
-    elif split:
-        kname = "score_split_kernel" if w.P == 128 else "score_block_kernel" if w.P <= 256 else \
-            "score_keys_kernel" if w.P < 512 else "score_split_wide_kernel"
-    else:
-        kname = "score_kernel"
+    kname = nacl.score_kernel(prob, cus=torch.cuda.get_device_properties(dev).multi_processor_count).split(",")[0]
     dom = {"kernel": kname, "bound": "hbm", "us": t_score,
            "achieved": ab["score"] / (t_score * 1e3), "peak": HBM_PEAK_GBS, "unit": "GB/s"}
     traffic = None

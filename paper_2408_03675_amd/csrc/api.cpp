@@ -218,44 +218,12 @@ struct KeyDraw {
   uint32_t layer = 0;
 };
 
-int run_score(const nacl_problem* p, const void* q, const void* k, const float* lse, float* scores,
-              char* ws, const Layout& l, const int* pos_dev, hipStream_t stream, const KeyDraw& kd = KeyDraw{}) {
-  nacl::ScoreLaunch s{};
-  s.args.B = p->B;
-  s.args.H = p->H;
-  s.args.L = p->L;
-  s.args.P = rows_of(p);  // proxy rows per K/V head
-  s.args.P0 = p->P;
-  s.args.qg = q_group_of(p);
-  for (int i = 0; i < 3; ++i) {
-    s.args.qs[i] = p->q_stride[i];
-    s.args.ks[i] = p->k_stride[i];
-  }
-  s.args.pos = pos_dev;
-  s.args.p_last = p->proxy_pos[p->P - 1];
-  s.args.c2 = (float)((double)p->sm_scale * 1.4426950408889634);
-  s.dtype = p->dtype;
-  s.D = p->D;
-  s.q = q;
-  s.k = k;
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return fail(NACL_ERR_HIP, "querying the device");
+// Which score kernel takes the call, and its items: sc.path, fused, tpw,
+// chunk_keys and n_psplit from the sizes and sc.lse_given.  (The few-row path,
+// score_uses_rows, comes before all of them where the library computes the
+// log-sum-exp.)
+void plan_score(const nacl_problem* p, int cus, nacl::ScoreSched& sc) {
   const int BH = p->B * p->H;
-  nacl::ScoreSched& sc = s.sched;
-  sc.lse_given = lse != nullptr;
-  uint32_t* words = reinterpret_cast<uint32_t*>(ws + l.cnt);
-  sc.queue = words;
-  sc.status = words + 1;
-  sc.head_cnt = words + kCounterHeader;
-  sc.scores = scores;
-  sc.gkeys = kd.on ? reinterpret_cast<uint32_t*>(ws + l.keys) : nullptr;
-  sc.g_mode = kd.sampling;
-  sc.g_k0 = (uint32_t)(kd.seed & 0xFFFFFFFFu);
-  sc.g_k1 = (uint32_t)(kd.seed >> 32);
-  sc.g_layer = kd.layer;
-  s.n_counter_words = l.n_counter_words;
   // Item size: the largest tpw whose items still number at least four per
   // resident work-group (two per CU); long items amortise the per-item Q
   // loads, partial stores and pipeline fill, too few leave a long tail.
@@ -327,6 +295,48 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
         sc.chunk_keys /= 2;
     }
   }
+}
+
+int run_score(const nacl_problem* p, const void* q, const void* k, const float* lse, float* scores,
+              char* ws, const Layout& l, const int* pos_dev, hipStream_t stream, const KeyDraw& kd = KeyDraw{}) {
+  nacl::ScoreLaunch s{};
+  s.args.B = p->B;
+  s.args.H = p->H;
+  s.args.L = p->L;
+  s.args.P = rows_of(p);  // proxy rows per K/V head
+  s.args.P0 = p->P;
+  s.args.qg = q_group_of(p);
+  for (int i = 0; i < 3; ++i) {
+    s.args.qs[i] = p->q_stride[i];
+    s.args.ks[i] = p->k_stride[i];
+  }
+  s.args.pos = pos_dev;
+  s.args.p_last = p->proxy_pos[p->P - 1];
+  s.args.c2 = (float)((double)p->sm_scale * 1.4426950408889634);
+  s.dtype = p->dtype;
+  s.D = p->D;
+  s.q = q;
+  s.k = k;
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return fail(NACL_ERR_HIP, "querying the device");
+  const int BH = p->B * p->H;
+  nacl::ScoreSched& sc = s.sched;
+  sc.lse_given = lse != nullptr;
+  uint32_t* words = reinterpret_cast<uint32_t*>(ws + l.cnt);
+  sc.queue = words;
+  sc.status = words + 1;
+  sc.head_cnt = words + kCounterHeader;
+  sc.scores = scores;
+  sc.gkeys = kd.on ? reinterpret_cast<uint32_t*>(ws + l.keys) : nullptr;
+  sc.g_mode = kd.sampling;
+  sc.g_k0 = (uint32_t)(kd.seed & 0xFFFFFFFFu);
+  sc.g_k1 = (uint32_t)(kd.seed >> 32);
+  sc.g_layer = kd.layer;
+  s.n_counter_words = l.n_counter_words;
+  plan_score(p, cus, sc);
+  const int passes = sc.lse_given ? 1 : 2;
   sc.n_chunks = (p->L + sc.chunk_keys - 1) / sc.chunk_keys;  // <= l.n_chunks
   sc.chunk_cnt = words + l.chunk_cnt_word;
   sc.colpart = reinterpret_cast<float*>(ws + l.colpart);
@@ -339,7 +349,7 @@ int run_score(const nacl_problem* p, const void* q, const void* k, const float* 
   sc.lse2 = reinterpret_cast<float*>(ws + l.lse);
   sc.lse_in = lse;
   sc.lse_mul = 1.4426950408889634f;
-  if (!sc.lse_given && nacl::score_uses_rows(p->dtype, p->D, rows)) {
+  if (!sc.lse_given && nacl::score_uses_rows(p->dtype, p->D, rows_of(p))) {
     // Few proxy rows: K is read once and the logits are kept (see score.hip).
     sc.logits = reinterpret_cast<float*>(ws + l.logits);
     sc.logits_stride = logits_stride(p);
@@ -500,6 +510,21 @@ extern "C" {
 size_t nacl_workspace_bytes(const nacl_problem* p) {
   if (check_problem(p) != NACL_OK) return 0;
   return layout_of(p).total;
+}
+
+// The score kernel that a call of these sizes takes on a device of cus compute
+// units (NULL for an invalid problem): for the benchmark's report and for tests,
+// which name the kernel they are for.
+const char* nacl_score_kernel(const nacl_problem* p, int lse_given, int cus) {
+  if (check_problem(p) != NACL_OK || cus < 1) return nullptr;
+  if (!lse_given && nacl::score_uses_rows(p->dtype, p->D, rows_of(p))) return "score_rows_logits_kernel";
+  nacl::ScoreSched sc{};
+  sc.lse_given = lse_given != 0;
+  plan_score(p, cus, sc);
+  if (sc.path == nacl::kScoreKeys) return sc.fused ? "score_keys_kernel, both passes" : "score_keys_kernel";
+  if (sc.path == nacl::kScoreTiles) return "score_kernel";
+  const int rows = rows_of(p);
+  return rows <= nacl::kSplitRows ? "score_split_kernel" : rows <= nacl::kBlockRows ? "score_block_kernel" : "score_split_wide_kernel";
 }
 
 int nacl_score(const nacl_problem* p, const void* q, const void* k, const float* lse, float* scores,

@@ -90,6 +90,8 @@ def load_library(path=LIB_PATH):
     lib.nacl_status_string.restype = ctypes.c_char_p
     lib.nacl_last_error_detail.argtypes = []
     lib.nacl_last_error_detail.restype = ctypes.c_char_p
+    lib.nacl_score_kernel.argtypes = [P, ctypes.c_int, ctypes.c_int]
+    lib.nacl_score_kernel.restype = ctypes.c_char_p
     lib.nacl_version.argtypes = []
     lib.nacl_version.restype = ctypes.c_int
     _lib = lib
@@ -225,6 +227,13 @@ def health(ws):
     reading them waits for the stream."""
     w = ws[4:12].view(torch.int32).cpu()
     return int(w[0]), int(w[1])
+
+
+def score_kernel(prob, lse=False, cus=256):
+    """Name of the kernel that scores a call of these sizes (lse: with the
+    caller's log-sum-exp) on a device of cus compute units."""
+    name = load_library().nacl_score_kernel(prob.ref(), int(bool(lse)), int(cus))
+    return None if name is None else name.decode()
 
 
 def score(prob, q, k, ws, lse=None, out=None):

@@ -1,0 +1,60 @@
+"""Which score kernel takes a call: the lines of the dispatch by rows, heads,
+length, type and the caller's log-sum-exp, on a device of 256 compute units
+(host only: no kernel runs).  The GPU tests name the kernel they are for and ask
+the library whether it is the one that runs."""
+
+import os
+
+import pytest
+
+nacl = pytest.importorskip("paper_2408_03675_amd.nacl")
+
+ROWS, HELD, KEYS = "score_rows_logits_kernel", "score_keys_kernel, both passes", "score_keys_kernel"
+SPLIT, BLOCK, WIDE, TILES = "score_split_kernel", "score_block_kernel", "score_split_wide_kernel", "score_kernel"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    if not os.path.exists(nacl.LIB_PATH):
+        pytest.skip("libnacl.so not built")
+
+
+def route(H, L, D, rows, dtype="bf16", lse=False, g=1, cus=256):
+    P = rows // g
+    return nacl.score_kernel(nacl.Problem(1, H, L, D, dtype, list(range(L - P, L)), q_group=g), lse, cus)
+
+
+@pytest.mark.parametrize("H,L,D,rows,plain,given", [
+    # few rows keep their logits; up to 64 rows (128 of D = 64) tiles; then by rows
+    (128, 32768, 128, 16, ROWS, TILES), (128, 32768, 128, 17, TILES, TILES), (128, 32768, 64, 8, ROWS, TILES),
+    (128, 32768, 64, 9, TILES, TILES), (128, 32768, 128, 64, TILES, TILES), (128, 32768, 128, 65, SPLIT, SPLIT),
+    (128, 32768, 128, 128, SPLIT, SPLIT), (128, 32768, 128, 129, BLOCK, BLOCK), (128, 32768, 128, 256, BLOCK, BLOCK),
+    (128, 32768, 128, 257, KEYS, KEYS), (128, 32768, 128, 384, KEYS, KEYS), (128, 32768, 128, 385, WIDE, KEYS),
+    (128, 32768, 128, 511, WIDE, KEYS), (128, 32768, 128, 512, WIDE, WIDE), (128, 32768, 128, 513, WIDE, WIDE),
+    (128, 32768, 64, 128, TILES, TILES), (128, 32768, 64, 129, KEYS, KEYS), (128, 32768, 64, 512, KEYS, KEYS),
+    (128, 32768, 64, 513, TILES, TILES),
+    # one 512-key chunk per CU, two for 65 to 128 rows: both passes with the keys held
+    (256, 512, 128, 17, HELD, TILES), (256, 513, 128, 64, TILES, TILES), (256, 1024, 128, 65, HELD, SPLIT),
+    (256, 1024, 128, 128, HELD, SPLIT), (257, 1024, 128, 65, SPLIT, SPLIT), (256, 1024, 128, 129, BLOCK, BLOCK),
+    (256, 512, 128, 512, HELD, KEYS), (257, 512, 128, 500, KEYS, KEYS), (256, 512, 64, 512, HELD, KEYS),
+    (1, 3000, 128, 600, WIDE, WIDE),
+    # 385 to 512 rows: more than one 2048-key item per CU, and enough rows for their number
+    (256, 2048, 128, 512, KEYS, KEYS), (257, 2048, 128, 512, WIDE, WIDE), (300, 1100, 128, 512, WIDE, KEYS),
+    (300, 2048, 128, 430, KEYS, KEYS), (320, 2048, 128, 410, WIDE, KEYS), (520, 2048, 128, 384, KEYS, KEYS),
+])
+def test_bf16_routes(H, L, D, rows, plain, given):
+    assert route(H, L, D, rows) == plain
+    assert route(H, L, D, rows, lse=True) == given
+
+
+@pytest.mark.parametrize("rows,plain", [(16, ROWS), (17, TILES), (300, TILES), (1000, TILES)])
+def test_f32_routes(rows, plain):
+    for H in (1, 128):
+        assert route(H, 4096, 128, rows, "f32") == plain
+        assert route(H, 4096, 128, rows, "f32", lse=True) == TILES
+
+
+def test_routes_count_grouped_rows_and_the_devices_cus():
+    assert route(128, 32768, 128, 200, g=4) == BLOCK
+    assert route(32, 4096, 128, 64, cus=256) == HELD and route(32, 4096, 128, 64, cus=128) == TILES
+    assert nacl.score_kernel(nacl.Problem(1, 1, 64, 96, "bf16", [1])) is None
