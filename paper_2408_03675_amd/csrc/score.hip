@@ -2483,7 +2483,7 @@ hipError_t launch_score(const ScoreLaunch& L, hipStream_t stream) {
     if (L.D == 128) {
       if (pb == 2) return launch_score_t<__bf16, 128, 2>(L, stream);
       if (pb == 4) return launch_score_t<__bf16, 128, 4>(L, stream);
-      return launch_score_t<__bf16, 128, 8>(L, stream);
+      return hipErrorInvalidValue;  // more than kSplitMin rows: the kernels above
     }
     if (pb == 2) return launch_score_t<__bf16, 64, 2>(L, stream);
     if (pb == 4) return launch_score_t<__bf16, 64, 4>(L, stream);

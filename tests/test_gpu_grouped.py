@@ -1,9 +1,9 @@
 """GPU parity of grouped-query scoring (several query heads per K/V head; the
 reading pinned in tests/test_oracle_grouped.py): each K/V head is scored by
 the proxy rows of its group's query heads, then selected and compacted like
-any head.  Every score kernel is covered (per-wave-tile below 128 proxy rows,
-the proxy-split kernel, its wide form from 512 rows), as are a caller-given
-log-sum-exp per query head and a whole eviction."""
+any head.  Small launches here (keys held through both passes, few rows, the wide
+split kernel, fp32 tiles), a caller-given log-sum-exp per query head and a whole
+eviction; every kernel of the larger ones in test_gpu_score_paths.py."""
 
 import sys
 

@@ -57,12 +57,12 @@ SCORE_CASES = [
     ("f32_single_proxy_mid", 1, 1, 2049, 128, "f32", [1500]),
     ("bf16_len1", 1, 1, 1, 64, "bf16", [0]),
     ("bf16_len17", 2, 1, 17, 128, "bf16", [16]),
-    # the proxy-split kernel (bf16, D = 128, P >= 128): scattered proxies over several
-    # 2048-key items with a ragged tail, and proxies early so later items lie past them
+    # small launches (keys held through both passes): scattered proxies over several chunks
+    # with a ragged tail, and proxies early so later chunks lie past them
     ("bf16_split_scattered", 1, 2, 5001, 128, "bf16", sorted(set(range(7, 5001, 31)))),
     ("bf16_split_early", 2, 1, 4100, 128, "bf16", list(range(200, 330))),
-    # exactly 128 proxies (the benchmark's proxy count): a ragged tail, scattered
-    # proxies, items past the last proxy, proxies at the start
+    # 128 proxies (the benchmark's proxy count) in small launches: a ragged tail, scattered
+    # proxies, chunks past the last proxy, proxies at the start
     ("bf16_p128_suffix", 2, 3, 1000, 128, "bf16", list(range(872, 1000))),
     ("bf16_p128_scattered", 1, 2, 5001, 128, "bf16", [7 + 39 * i for i in range(128)]),
     ("bf16_p128_early", 2, 1, 4100, 128, "bf16", list(range(200, 328))),
@@ -120,9 +120,9 @@ def test_score_strided_inputs(pos):
 def test_score_with_caller_lse(P):
     """With the caller's log-sum-exp (Appendix A.7, Algorithm 2) only the
     column reduction runs and gives the same scores (P = 3: a few-row problem,
-    which with a caller LSE takes the per-wave-tile kernel's single pass;
-    P = 160: the proxy-split kernel, a full and a partial proxy group; P = 700:
-    the wide kernel, a full and a partial group of 512)."""
+    which with a caller LSE takes the per-wave-tile kernel's single pass, as
+    P = 40 does; P = 160: the block kernel; P = 700: the wide kernel, a full and
+    a partial group of 512)."""
     w = custom("lse", 1, 3, 1500, 128, P, dtype="bf16", data_seed=3)
     q, k, v = make_layer(w, 0, device="cuda")
     pos = w.proxy_pos
@@ -135,13 +135,13 @@ def test_score_with_caller_lse(P):
 
 @pytest.mark.parametrize("P", [100, 128, 160, 600])
 def test_score_overflow_takes_exact_path(P):
-    """Pass 1 sums exp2(logit - r) against the maximum r of the first tile of
-    each item's key range; a later key far above r overflows fp32, and the
-    kernel recomputes that range's sums against its exact maximum.  Here one
-    key per head sits about 180 (natural-log units) above every other logit
-    of its range, so the fast path overflows and the scores are dominated by
-    that key (P = 100: the per-wave-tile kernel; P = 128 and 160: the
-    proxy-split kernel; P = 600: its wide form)."""
+    """Pass 1 of most score kernels sums exp2(logit - r) against the maximum r of
+    the first tile of each item's key range; a later key far above r overflows
+    fp32, and the kernel recomputes that range's sums against its exact
+    maximum.  Here one key per head sits about 180 (natural-log units) above
+    every other logit of its range, so the scores are dominated by that key
+    (P = 600: the wide split kernel; the others, small launches, hold the keys
+    and take exact maxima.  The other kernels: test_gpu_score_paths.py)."""
     B, H, L, D = 1, 2, 3000, 128
     g = torch.Generator(device="cuda").manual_seed(11)
     q = torch.randn((B, H, L, D), generator=g, device="cuda")

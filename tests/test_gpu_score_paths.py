@@ -17,7 +17,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import SAMPLE_SOFTMAX, proxy_scores
+from oracle import SAMPLE_SOFTMAX, proxy_scores, proxy_scores_grouped
 from synth import custom, make_layer
 from tests._parity import check_scores
 
@@ -35,6 +35,17 @@ def _gpu():
 
 def _np(t):
     return t.detach().float().cpu().numpy()
+
+
+KERNELS = {"held": "score_keys_kernel, both passes", "queued": "score_keys_kernel", "split": "score_split_kernel",
+           "block": "score_block_kernel", "wide": "score_split_wide_kernel", "tiles": "score_kernel",
+           "few": "score_rows_logits_kernel"}
+
+
+def check_kernel(name, prob):
+    """The case runs the kernel that its name says."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert nacl.score_kernel(prob, cus=cus) == KERNELS[name.split("_")[0]], name
 
 
 def suffix(L, P):
@@ -62,6 +73,13 @@ CASES = [
     ("held_twice_128_rows_d64", 1, 170, 1030, 64, spread(1030, 128)),
     # beyond those: tiles, split with short items, block, keys with queued passes, wide
     ("tiles_64_rows", 2, 86, 1100, 128, suffix(1100, 64)),
+    ("tiles_24_rows", 2, 45, 1100, 128, spread(1100, 24)),
+    ("tiles_28_rows_d64", 2, 45, 1100, 64, suffix(1100, 28)),
+    ("tiles_60_rows_d64", 1, 90, 1045, 64, list(range(30, 90))),
+    ("tiles_128_rows_d64", 1, 175, 1100, 64, spread(1100, 128)),
+    ("tiles_513_rows_d64", 1, 2, 1100, 64, suffix(1100, 513)),
+    # long items, later ones past the last proxy
+    ("split_128_items_past_the_proxies", 1, 100, 5000, 128, list(range(200, 328))),
     ("split_128_short_items", 2, 90, 1100, 128, spread(1100, 128)),
     ("split_65_rows", 2, 130, 1100, 128, suffix(1100, 65)),
     ("split_97_rows", 3, 61, 1500, 128, spread(1500, 97)),
@@ -93,11 +111,12 @@ def test_score_paths_match_oracle(case):
     w = custom(name, B, H, L, D, len(pos), dtype="bf16", data_seed=zlib.crc32(name.encode()) % 1000)
     q, k, v = make_layer(w, 0, device="cuda")
     prob = nacl.Problem.from_tensors(q, k, v, pos)
+    check_kernel(name, prob)
     ws = nacl.workspace(prob)
     F = nacl.score(prob, q, k, ws).clone()
     again = nacl.score(prob, q, k, ws)
     assert torch.equal(F, again)
-    heads = range(0, H, 1 if L < 4000 else 43)  # the oracle over the long case's heads takes minutes
+    heads = range(0, H, 1 if L < 4000 else 33)  # the oracle over the long case's heads takes minutes
     qn, kn = _np(q[:, heads]), _np(k[:, heads])
     Fr, lse = proxy_scores(qn, kn, pos, prob.c.sm_scale)
     check_scores(_np(F[:, heads]), Fr, name)
@@ -134,6 +153,64 @@ def test_score_paths_large_logits(H, P, D):
     np.testing.assert_allclose(_np(F).astype(np.float64).sum(-1), P, rtol=1e-5)
 
 
+@pytest.mark.parametrize("H,P,D,dt", [(90, 24, 128, "bf16"), (90, 64, 128, "bf16"), (90, 20, 64, "bf16"), (90, 60, 64, "bf16"),
+                                      (180, 100, 64, "bf16"), (3, 600, 64, "bf16"), (3, 40, 128, "f32"), (3, 30, 64, "f32"),
+                                      (3, 60, 64, "f32")])
+def test_tile_kernel_large_logits(H, P, D, dt):
+    """The same for each form of the per-wave-tile kernel (two, four and eight
+    blocks of rows, both types), which recomputes such a range's sums against
+    its exact maximum."""
+    L = 1100
+    g = torch.Generator(device="cuda").manual_seed(12)
+    q, k = (torch.randn((1, H, L, D), generator=g, device="cuda") for _ in range(2))
+    pos = suffix(L, P)
+    q[:, :, L - P:] += 2.0 * (128 / D) ** 0.5
+    k[:, ::2, 400] = 8.0
+    k[:, 1::2, 700 if P < 400 else 480] = 8.0
+    q, k = (x.to(torch.bfloat16 if dt == "bf16" else torch.float32) for x in (q, k))
+    prob = nacl.Problem.from_tensors(q, k, k, pos)
+    check_kernel("tiles", prob)
+    F = nacl.score(prob, q, k, nacl.workspace(prob))
+    heads = [0, 1, H - 1]
+    Fr, _ = proxy_scores(_np(q[:, heads]), _np(k[:, heads]), pos, prob.c.sm_scale)
+    check_scores(_np(F[:, heads]), Fr, "large logits")
+    np.testing.assert_allclose(_np(F).astype(np.float64).sum(-1), P, rtol=1e-5)
+
+
+GROUPED_CASES = [
+    # name, B, H (K/V heads), q_group, L, D, P: [B, L, H, D] layout, rows = q_group * P
+    ("held_192", 2, 4, 4, 3000, 128, 48), ("held_90_d64", 2, 3, 3, 1037, 64, 30),
+    ("split_100", 2, 90, 2, 1100, 128, 50), ("block_200", 2, 45, 4, 1100, 128, 50), ("queued_320", 1, 90, 8, 1100, 128, 40),
+    ("queued_200_d64", 1, 90, 4, 1100, 64, 50), ("wide_560", 1, 4, 8, 1100, 128, 70), ("wide_416", 1, 400, 8, 600, 128, 52),
+    ("tiles_48", 2, 45, 2, 1100, 128, 24), ("tiles_28_d64", 1, 90, 2, 1100, 64, 14), ("tiles_100_d64", 1, 180, 4, 1100, 64, 25),
+    ("tiles_560_d64", 1, 2, 8, 1100, 64, 70),
+]
+
+
+@pytest.mark.parametrize("case", GROUPED_CASES, ids=[c[0] for c in GROUPED_CASES])
+def test_score_paths_grouped_and_strided(case):
+    """Grouped query heads with rows of Q and K that lie between other heads'
+    rows, with the library's and the caller's log-sum-exp."""
+    name, B, H, g, L, D, P = case
+    print("grouped path", name, file=sys.stderr, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(P + H)
+    q = torch.randn((B, L, H * g, D), generator=gen, device="cuda").to(torch.bfloat16).permute(0, 2, 1, 3)
+    k = torch.randn((B, L, H, D), generator=gen, device="cuda").to(torch.bfloat16).permute(0, 2, 1, 3)
+    pos = spread(L - 3, P)
+    prob = nacl.Problem.from_tensors(q, k, k, pos)
+    check_kernel(name, prob)
+    ws = nacl.workspace(prob)
+    F = nacl.score(prob, q, k, ws)
+    heads = sorted({0, H // 2, H - 1})
+    Fr, lse = proxy_scores_grouped(_np(q.unflatten(1, (H, g))[:, heads].flatten(1, 2)), _np(k[:, heads]), pos, prob.c.sm_scale, g)
+    check_scores(_np(F[:, heads]), Fr, name)
+    np.testing.assert_allclose(_np(F).astype(np.float64).sum(-1), len(pos) * g, rtol=1e-5)
+    given = torch.zeros((B, H, g, len(pos)), device="cuda")
+    given[:, heads] = torch.from_numpy(lse.astype(np.float32)).cuda().reshape(B, len(heads), g, len(pos))
+    F = nacl.score(prob, q, k, ws, lse=given.flatten(1, 2).contiguous())
+    check_scores(_np(F[:, heads]), Fr, name + " caller lse")
+
+
 ODD_CASES = [
     # name, H, L, D, P, dtype: one case per kernel
     ("held_200", 2, 1100, 128, 200, "bf16"), ("held_40_d64", 2, 1100, 64, 40, "bf16"), ("queued_300", 90, 1100, 128, 300, "bf16"),
@@ -154,6 +231,7 @@ def test_score_odd_row_stays_below_its_position(case):
     pos = spread(L - 90, P)
     P = len(pos)
     prob = nacl.Problem.from_tensors(q, k, k, pos)
+    check_kernel(name, prob)
     ws = nacl.workspace(prob)
     heads = [0, H - 1]
     Fr, lse = proxy_scores(_np(q[:, heads]), _np(k[:, heads]), pos, prob.c.sm_scale)
