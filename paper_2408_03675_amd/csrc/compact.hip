@@ -67,22 +67,25 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(CompactLaunch 
 // work-groups: few heads still give enough loads in flight.  What bounds it is
 // memory latency (a chunk's indices, its rows, then the stores) until every CU
 // has work, and then HBM; a chunk's indices are read together, as a row's load
-// behind its own index only would wait for them one by one.  Whole rows and
-// indices one by one before, now: 4 heads of 131072 rows keeping 40000 (bf16,
-// 128) 368 -> 89 us; 32 heads, 32768 keeping 10000, 148 -> 67 (4.9 TB/s); 12
-// fp32 heads, 20001 keeping 7001, 135 -> 33; 128 heads, 16384 keeping 5000 (bf16,
-// 64) 63.6 -> 59.2; 128 heads, 6617 keeping 6553, 184 -> 182.
+// behind its own index only would wait for them one by one.  Whole rows of 1024
+// threads and indices one by one before, now (a call on buffers that are not in a
+// cache): 4 heads of 131072 rows keeping 40000 (bf16, 128) 519 -> 140 us; 32
+// heads, 32768 keeping 10000, 170 -> 74 (4.4 TB/s); 12 fp32 heads, 20001 keeping
+// 7001, 199 -> 46; 128 heads, 16384 keeping 5000 (bf16, 64) 75 -> 71; 128 heads,
+// 6617 keeping 6553, 181 -> 175.
 constexpr int kInplaceVecs = 16;  // vectors per thread and chunk (all loads in flight at once)
 
-template <int VPR, int SLICE, int THREADS>
-__global__ __launch_bounds__(THREADS) void compact_inplace_kernel(CompactLaunch a) {
-  static_assert(VPR % SLICE == 0 && THREADS % SLICE == 0);
+constexpr int kInplaceThreads = 512;
+
+template <int VPR, int SLICE>
+__global__ __launch_bounds__(kInplaceThreads) void compact_inplace_kernel(CompactLaunch a) {
+  static_assert(VPR % SLICE == 0 && kInplaceThreads % SLICE == 0);
   const int bh = blockIdx.x, b = bh / a.H, h = bh % a.H;
   const bool is_v = blockIdx.y % 2 != 0;
   const int col = (int)(blockIdx.y / 2) * SLICE;
   const int64_t* st = is_v ? a.vs : a.ks;
   u32x4* base = static_cast<u32x4*>(is_v ? a.v_out : a.k_out) + b * st[0] + h * st[1] + col + threadIdx.x % SLICE;
-  constexpr int kRows = THREADS / SLICE;  // rows per vector of a thread
+  constexpr int kRows = kInplaceThreads / SLICE;  // rows per vector of a thread
   const int32_t* keep = a.keep + (int64_t)bh * a.C;
   for (int c0 = 0; c0 < a.C; c0 += kRows * kInplaceVecs) {
     u32x4 x[kInplaceVecs];
@@ -200,14 +203,16 @@ hipError_t launch_compact_t(const CompactLaunch& a, hipStream_t stream) {
   if (a.in_place) {
     // Slices of 64 bytes while these give at most one work-group per CU (256);
     // beyond, a line shared by two work-groups costs more than the parallelism
-    // gives, and slices are whole 128-byte lines.  64 against 128 bytes: 32
-    // heads of 16 vectors a row (256 work-groups) 66.6 against 80.9 us, 128
-    // heads 306 against 187.
+    // gives (32 heads of 16 vectors a row, 256 work-groups: 66.6 us in 64-byte
+    // slices, 80.9 in 128-byte ones; 128 heads 306 and 187), and work-groups take
+    // whole rows: 128 heads of 2048 rows (bf16, 128) keeping 2000 54.5 us, in
+    // 128-byte slices with 1024 threads 62.7; 1000 of 600 keeping 200 46 and 60,
+    // fp32 88 and 116; 400 of 2000 keeping 1000 92 and 89.
     const int BH = a.B * a.H;
     if ((int64_t)2 * BH * (VPR / 4) <= 256)
-      hipLaunchKernelGGL((compact_inplace_kernel<VPR, 4, 512>), dim3(BH, 2 * (VPR / 4)), dim3(512), 0, stream, a);
+      hipLaunchKernelGGL((compact_inplace_kernel<VPR, 4>), dim3(BH, 2 * (VPR / 4)), dim3(kInplaceThreads), 0, stream, a);
     else
-      hipLaunchKernelGGL((compact_inplace_kernel<VPR, 8, 1024>), dim3(BH, 2 * (VPR / 8)), dim3(1024), 0, stream, a);
+      hipLaunchKernelGGL((compact_inplace_kernel<VPR, VPR>), dim3(BH, 2), dim3(kInplaceThreads), 0, stream, a);
     return hipGetLastError();
   }
   constexpr int rows_per_block = kCompactThreads / VPR;

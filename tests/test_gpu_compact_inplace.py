@@ -26,6 +26,11 @@ pytestmark = pytest.mark.gpu
     (127, 600, 129, 64, "bf16", False),
     (128, 600, 512, 128, "bf16", False),
     (257, 300, 131, 128, "bf16", False),
+    # whole rows: chunks of 1024, 512 and 256 rows (8, 16 and 32 vectors a row) and one more
+    (130, 1100, 1025, 64, "bf16", False),
+    (65, 600, 513, 128, "bf16", True),
+    (40, 400, 257, 128, "f32", False),
+    (300, 300, 256, 128, "f32", False),
 ])
 def test_in_place_slices(heads, L, C, D, dt, blhd):
     print("in place", heads, L, C, D, dt, blhd, flush=True)
