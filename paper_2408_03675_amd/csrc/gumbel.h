@@ -12,6 +12,19 @@
 
 namespace nacl {
 
+// A binary64 constant made where it stands.  As plain constants the compiler
+// keeps those of the logarithms in registers from the start of a kernel on (18
+// vector and 18 scalar ones), and the score kernels, which draw keys at the end
+// of their items only, spilled others for them: 32 heads of 32k keys, 128 rows
+// 171 us with, 151 without; a whole eviction of 128 such heads 573 and 558.
+template <uint64_t BITS>
+__device__ __forceinline__ double constant_here() {
+  uint32_t lo, hi;
+  asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %3" : "=&v"(lo), "=v"(hi) : "n"((uint32_t)BITS), "n"((uint32_t)(BITS >> 32)));
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+#define NACL_HERE(x) constant_here<__builtin_bit_cast(uint64_t, (double)(x))>()
+
 // ln(x) in binary64 for x >= 0 (ln 0 = -inf, ln inf = inf), to within a
 // few units in the last place: x = m 2^e with m in [sqrt(1/2), sqrt(2)),
 // ln m = 2 atanh(s) with s = (m - 1) / (m + 1), |s| < 0.172, summed as the
@@ -39,16 +52,16 @@ __device__ __forceinline__ double ln_f64(double x) {
   double s = f * r;
   s = fma(fma(-s, d, f), r, s);
   const double z = s * s;
-  double q = 1.0 / 21;
-  q = fma(q, z, 1.0 / 19);
-  q = fma(q, z, 1.0 / 17);
-  q = fma(q, z, 1.0 / 15);
-  q = fma(q, z, 1.0 / 13);
-  q = fma(q, z, 1.0 / 11);
-  q = fma(q, z, 1.0 / 9);
-  q = fma(q, z, 1.0 / 7);
-  q = fma(q, z, 1.0 / 5);
-  q = fma(q, z, 1.0 / 3);
+  double q = NACL_HERE(1.0 / 21);
+  q = fma(q, z, NACL_HERE(1.0 / 19));
+  q = fma(q, z, NACL_HERE(1.0 / 17));
+  q = fma(q, z, NACL_HERE(1.0 / 15));
+  q = fma(q, z, NACL_HERE(1.0 / 13));
+  q = fma(q, z, NACL_HERE(1.0 / 11));
+  q = fma(q, z, NACL_HERE(1.0 / 9));
+  q = fma(q, z, NACL_HERE(1.0 / 7));
+  q = fma(q, z, NACL_HERE(1.0 / 5));
+  q = fma(q, z, NACL_HERE(1.0 / 3));
   const double s2 = 2.0 * s;
   const double lnm = fma(s2 * z, q, s2);
   const double ed = (double)e;
@@ -58,6 +71,17 @@ __device__ __forceinline__ double ln_f64(double x) {
   if (x == 0.0) return -INFINITY;
   if (x == INFINITY) return INFINITY;
   return res;
+}
+
+struct LnConstants {
+  double ln2_hi, ln2_lo;  // 32 leading bits of ln 2, and the rest
+  double q[7];            // the polynomial's coefficients, highest first
+};
+__device__ __forceinline__ LnConstants ln_constants() {
+  return LnConstants{NACL_HERE(0.6931471803691238),   NACL_HERE(1.9082149292705877e-10),
+                     {NACL_HERE(0.07308292712444311), NACL_HERE(0.07665855309105386), NACL_HERE(0.09091444727837474),
+                      NACL_HERE(0.11111105565129939), NACL_HERE(0.14285714313001635), NACL_HERE(0.19999999999949722),
+                      NACL_HERE(0.3333333333333335)}};
 }
 
 // ln(x) - bias ln 2 in binary64 for positive finite normal x: the logarithm of
@@ -72,9 +96,7 @@ __device__ __forceinline__ double ln_f64(double x) {
 // 6e7 draws, both tails included: largest relative error 2.22e-16 (ln_f64
 // 2.27e-16), mean error of a key 7.88e-17 (8.02e-17), the same binary32 keys.
 // 4.2 M keys: 18.4 us before, now 14.7.
-__device__ __forceinline__ double ln_pos_f64(double x, int bias) {
-  constexpr double kLn2Hi = 0.6931471803691238;                // 32 leading bits of ln 2
-  constexpr double kLn2Lo = 1.9082149292705877e-10;            // ln 2 - kLn2Hi
+__device__ __forceinline__ double ln_pos_f64(double x, int bias, const LnConstants& c) {
   const uint64_t bits = __builtin_bit_cast(uint64_t, x);
   const uint32_t hi = (uint32_t)(bits >> 32);
   const uint32_t t = hi - 0x3FE6A09Eu;                         // mantissa into [sqrt(1/2), sqrt(2))
@@ -86,24 +108,22 @@ __device__ __forceinline__ double ln_pos_f64(double x, int bias) {
   double s = f * r;
   s = fma(fma(-s, d, f), r, s);
   const double z = s * s;
-  double q = 0.07308292712444311;
-  q = fma(q, z, 0.07665855309105386);
-  q = fma(q, z, 0.09091444727837474);
-  q = fma(q, z, 0.11111105565129939);
-  q = fma(q, z, 0.14285714313001635);
-  q = fma(q, z, 0.19999999999949722);
-  q = fma(q, z, 0.3333333333333335);
+  double q = c.q[0];
+#pragma unroll
+  for (int i = 1; i < 7; ++i) q = fma(q, z, c.q[i]);
   const double s2 = s + s;
-  return fma(e, kLn2Hi, s2 + fma(s2 * z, q, e * kLn2Lo));
+  return fma(e, c.ln2_hi, s2 + fma(s2 * z, q, e * c.ln2_lo));
 }
+
+#undef NACL_HERE
 
 // Key of one token.  MODE selects the log-weight: 0 = F (weights
 // Softmax(F)), 1 = ln F (weights F), 2 = none (uniform).
 template <int MODE>
-__device__ __forceinline__ uint32_t gumbel_order_key(float f, uint32_t word) {
+__device__ __forceinline__ uint32_t gumbel_order_key(float f, uint32_t word, const LnConstants& c) {
   // word + 1/2, from the bits of 2^52 + word.
   const double u32 = __builtin_bit_cast(double, 0x4330000000000000ull | word) - (0x1p52 - 0.5);
-  const double g = -ln_pos_f64(-ln_pos_f64(u32, 32), 0);
+  const double g = -ln_pos_f64(-ln_pos_f64(u32, 32, c), 0, c);
   double key = g;
   if constexpr (MODE == 0) key = (double)f + g;
   if constexpr (MODE == 1) key = ln_f64((double)f) + g;
@@ -118,12 +138,13 @@ __device__ __forceinline__ void gumbel_block_keys(int mode, int j0, int n, int b
                                                   uint32_t (&out)[4]) {
   const U32x4 w = philox4x32_10(U32x4{(uint32_t)(j0 >> 2), (uint32_t)h, (uint32_t)b, layer}, k0, k1);
   const uint32_t word[4] = {w.x, w.y, w.z, w.w};
+  const LnConstants c = ln_constants();
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     if (e < n) {
-      if (mode == 0) out[e] = gumbel_order_key<0>(f[e], word[e]);
-      else if (mode == 1) out[e] = gumbel_order_key<1>(f[e], word[e]);
-      else out[e] = gumbel_order_key<2>(f[e], word[e]);
+      if (mode == 0) out[e] = gumbel_order_key<0>(f[e], word[e], c);
+      else if (mode == 1) out[e] = gumbel_order_key<1>(f[e], word[e], c);
+      else out[e] = gumbel_order_key<2>(f[e], word[e], c);
     }
   }
 }

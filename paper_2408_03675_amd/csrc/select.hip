@@ -74,9 +74,10 @@ __global__ __launch_bounds__(256) void gumbel_keys_kernel(const float* __restric
   }
   const U32x4 w = philox4x32_10(U32x4{(uint32_t)blk, (uint32_t)h, (uint32_t)b, layer}, k0, k1);
   const uint32_t word[4] = {w.x, w.y, w.z, w.w};
+  const LnConstants c = ln_constants();
   uint32_t kv[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) kv[e] = gumbel_order_key<MODE>(fv[e], word[e]);
+  for (int e = 0; e < 4; ++e) kv[e] = gumbel_order_key<MODE>(fv[e], word[e], c);
   if (vec) {
     *reinterpret_cast<uint4*>(out) = uint4{kv[0], kv[1], kv[2], kv[3]};
   } else {
