@@ -246,6 +246,12 @@ void plan_score(const nacl_problem* p, int cus, nacl::ScoreSched& sc) {
     // 55 against 66), fewer rows do not (64 rows: 50 against 44; the tile
     // kernel holds up to 64 with twice the work-groups) nor do more (200 rows,
     // 400 chunks: 66.6, in the block kernel 62.4).
+    // Two blocks of rows (of D = 64, one) on at most an eighth of the CUs stay with
+    // the tile kernel, whose items start sooner: 1 head of 1024 keys, 17 rows 17.4
+    // us, held 20.4, 32 rows 17.5 and 18.4; 4 heads of 2048, 17 rows 18.8 and 20.2,
+    // 36 21.2 and 20.6; 8 heads, 32 rows 19.8 and 19.3; D = 64, 4 heads of 2048, 9
+    // rows 18.1 and 19.4, 16 17.3 and 17.5.
+    const bool few = rows <= p->D / 4 && items_of(nacl::kKeysThreads) <= cus / 8;
     const bool two = rows > nacl::kKeysTwoMin && rows <= nacl::kKeysTwoMax;
     // 257 to 512 rows of D = 128: the wide kernel pads them to 512, so it takes
     // them from the number on where that costs less than its pipeline gains, and
@@ -261,7 +267,7 @@ void plan_score(const nacl_problem* p, int cus, nacl::ScoreSched& sc) {
                       (sc.lse_given ? rows == nacl::kSplitWideRows && p->L >= nacl::kSplitChunkKeys
                                     : rows > 384 && rows * items > (int64_t)nacl::kSplitWideRows * cus);
     const int64_t fuse_max = std::min<int64_t>((two ? 2 : 1) * (int64_t)cus, nacl::kKeysFuseMax);
-    if (!sc.lse_given && rows <= nacl::kSplitWideRows && items_of(nacl::kKeysThreads) <= fuse_max) {
+    if (!sc.lse_given && !few && rows <= nacl::kSplitWideRows && items_of(nacl::kKeysThreads) <= fuse_max) {
       sc.path = nacl::kScoreKeys;
       sc.fused = 1;
       sc.chunk_keys = nacl::kKeysThreads;

@@ -59,8 +59,10 @@ def spread(L, P):
 CASES = [
     # name, B, H, L, D, positions
     # both passes in one work-group: rows about a multiple of 32 and of the row buffers
-    ("held_17_rows", 1, 3, 513, 128, suffix(513, 17)),
+    ("held_17_rows", 1, 17, 1025, 128, suffix(1025, 17)),
+    ("tiles_32_rows_few_chunks", 1, 3, 513, 128, suffix(513, 32)),
     ("held_32_rows_d64", 2, 2, 511, 64, spread(511, 32)),
+    ("held_32_rows", 1, 33, 511, 128, spread(511, 32)),
     ("held_33_rows", 1, 2, 512, 128, spread(512, 33)),
     ("held_127_rows_d64", 1, 2, 1025, 64, suffix(1025, 127)),
     ("held_129_rows", 1, 2, 1537, 128, spread(1537, 129)),
@@ -73,6 +75,8 @@ CASES = [
     ("held_twice_128_rows_d64", 1, 170, 1030, 64, spread(1030, 128)),
     # beyond those: tiles, split with short items, block, keys with queued passes, wide
     ("tiles_64_rows", 2, 86, 1100, 128, suffix(1100, 64)),
+    ("tiles_24_rows_few_chunks", 1, 4, 2048, 128, spread(2048, 24)),
+    ("tiles_16_rows_d64_few_chunks", 1, 3, 513, 64, suffix(513, 16)),
     ("tiles_24_rows", 2, 45, 1100, 128, spread(1100, 24)),
     ("tiles_28_rows_d64", 2, 45, 1100, 64, suffix(1100, 28)),
     ("tiles_60_rows_d64", 1, 90, 1045, 64, list(range(30, 90))),

@@ -34,7 +34,8 @@ def route(H, L, D, rows, dtype="bf16", lse=False, g=1, cus=256):
     (128, 32768, 64, 128, TILES, TILES), (128, 32768, 64, 129, KEYS, KEYS), (128, 32768, 64, 512, KEYS, KEYS),
     (128, 32768, 64, 513, TILES, TILES),
     # one 512-key chunk per CU, two for 65 to 128 rows: both passes with the keys held
-    (256, 512, 128, 17, HELD, TILES), (256, 513, 128, 64, TILES, TILES), (256, 1024, 128, 65, HELD, SPLIT),
+    (256, 512, 128, 17, HELD, TILES), (33, 512, 128, 17, HELD, TILES), (32, 512, 128, 32, TILES, TILES),
+    (32, 512, 128, 33, HELD, TILES), (4, 2048, 64, 16, TILES, TILES), (4, 2048, 64, 17, HELD, TILES), (256, 513, 128, 64, TILES, TILES), (256, 1024, 128, 65, HELD, SPLIT),
     (256, 1024, 128, 128, HELD, SPLIT), (257, 1024, 128, 65, SPLIT, SPLIT), (256, 1024, 128, 129, BLOCK, BLOCK),
     (256, 512, 128, 512, HELD, KEYS), (257, 512, 128, 500, KEYS, KEYS), (256, 512, 64, 512, HELD, KEYS),
     (1, 3000, 128, 600, WIDE, WIDE),
