@@ -88,7 +88,7 @@ struct ScoreArgs {
 // Work queue of the persistent score kernel (see score.hip).
 struct ScoreSched {
   int tpw;               // tiles of 16 keys per wave and item (multiple of 4)
-  int chunk_keys;        // keys per item: kScoreWaves * tpw * 16
+  int chunk_keys;        // keys per item (kScoreTiles: kScoreWaves * tpw * 16)
   int n_chunks;          // key chunks per head
   int heads_per_group;   // heads per scheduling group
   int n_groups;          // B*H / heads_per_group

@@ -366,10 +366,10 @@ def test_evict_draws_the_same_keys_as_select(mode, where, P):
     run on the same scores, which draws every key in its own kernel.  Proxies
     at the end, or early so that whole chunks lie past the last proxy (scores
     0, keys drawn on the zero path); L not a multiple of 4; every non-protected
-    slot random, so every key's value matters.  P = 160 runs the proxy-split
-    score kernel on one proxy group (P = 128) and on a full and a partial group
-    (P = 160), P = 40 the per-wave-tile one, P = 1 and 6 the few-row path
-    (keys drawn by its column kernel)."""
+    slot random, so every key's value matters.  P = 1 and 6 take the few-row
+    path (keys drawn by its column kernel), P = 40, 128 and 160 the kernel that
+    holds its keys (108 chunks of 512); the other score kernels' draws are
+    compared in test_gpu_score_paths.py."""
     B, H, L, D = 2, 3, 9001, 128
     pos = list(range(L - P, L)) if where == "end" else list(range(300, 300 + P))
     _say("evict keys", mode, where, P)
