@@ -636,7 +636,8 @@ int nacl_attention(const nacl_problem* p, const void* q, const void* k, const vo
   if (lse_proxy && !p->proxy_pos_dev)
     return fail(NACL_ERR_INVALID_ARG, "lse_proxy needs proxy_pos_dev (the proxy rows on the device)");
   // Each head's rows are addressed through buffer descriptors with 32-bit
-  // byte offsets, up to 127 rows past L.
+  // byte offsets, up to 127 rows past L (255 from 6144 rows on, whose row
+  // strides are at most 2^31 / 6144 bytes): below 2^32 either way.
   const int64_t rows[3] = {p->q_stride[2], p->k_stride[2], p->v_stride[2]};
   for (int t = 0; t < 3; ++t) {
     if (rows[t] < p->D) return fail(NACL_ERR_INVALID_ARG, "attention needs row strides of at least D");
